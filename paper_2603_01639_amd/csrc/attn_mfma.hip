@@ -996,14 +996,16 @@ __global__ void __launch_bounds__(kThreads, 1) attn_split_kernel(MfmaArgs a) {
 // takes split s's (m, l); the 4 groups of 16 lanes each read one split's row
 // (16 bytes = 8 dims per lane) per step, so 4 splits' rows are in flight per
 // load, and the groups' sums are added with two lane exchanges.  The kernel
-// is latency-bound, so the (m, l) pairs and the first 16 splits' rows are
+// is latency-bound, so the (m, l) pairs and the first 32 splits' rows are
 // requested before the sequence's prefix length and node count arrive: every
 // row of the grid is inside the workspace's Mpad rows, and every split index
-// below max_splits inside its splits.
+// below max_splits inside its splits.  (A second round for the splits past 16
+// and reductions through the LDS crossbar made it 5.0 us instead of 4.1 for
+// 240 rows of 17 splits on 8 kv heads.)
 template <int HD>
 __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
   __shared__ float w_s[4][kMaxMergeSplits];
-  constexpr int kFirst = 16;  // splits whose rows are requested up front
+  constexpr int kFirst = 32;  // splits whose rows are requested up front
   const int bg = blockIdx.x;
   const int b = bg / a.Hkv;
   const int g = bg % a.Hkv;
@@ -1034,7 +1036,7 @@ __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
   if (n_splits == 1) return;  // the attention kernel wrote this row's output
   float M = lane < n_splits ? ml0.x : -INFINITY;
   for (int s = lane + kWave; s < n_splits; s += kWave) M = fmaxf(M, a.ws_ml[(part0 + s * Mpad) * 2]);
-  M = wave_max(M);
+  M = wave_max_dpp(M);
   float wsum = 0.f;
   for (int s = lane; s < n_splits; s += kWave) {
     const f32x2 ml = s == lane ? ml0 : *reinterpret_cast<const f32x2*>(a.ws_ml + (part0 + s * Mpad) * 2);
@@ -1042,7 +1044,7 @@ __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
     w_s[wv][s] = w;
     wsum += w;
   }
-  wsum = wave_sum(wsum);
+  wsum = wave_sum_dpp(wsum);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1077,8 +1079,8 @@ __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
   }
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    acc[e] += __shfl_xor(acc[e], 16, kWave);
-    acc[e] += __shfl_xor(acc[e], 32, kWave);
+    acc[e] += lane_xor_f<16>(acc[e], lane);
+    acc[e] += lane_xor_f<32>(acc[e], lane);
   }
   if (grp == 0 && col < HD / 8) {  // (lanes past the head's dims summed unused workspace)
     const float inv = 1.f / wsum;
@@ -1094,6 +1096,71 @@ __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
   }
 }
 
+
+// The split plan's merge when every unit has at most kFewSplits splits: 16
+// lanes take a row (16 bytes of each split's row a lane) and 16 rows a
+// workgroup, with every split's (max, sum) pair (one address for the 16
+// lanes) and row chunk in flight at once; each lane then weights the splits
+// itself, with no exchange between lanes.  Few splits mean many row tiles
+// (long trees), where a wave per row is bound by its instructions: 2048 rows
+// of 4 splits on 8 kv heads take 5.7 us here and 9.7 us there.  From 9 splits
+// on the rows are few, and a wave per row keeps more loads in flight.
+constexpr int kFewSplits = 8;
+template <int HD>
+__global__ void __launch_bounds__(256) attn_split_merge_few_kernel(MfmaArgs a) {
+  const int bg = blockIdx.x;
+  const int b = bg / a.Hkv;
+  const int g = bg % a.Hkv;
+  if (halted(a.status)) return;
+  const int row = blockIdx.y * 16 + threadIdx.x / 16;  // below row_tiles * kTileRows
+  const int col = threadIdx.x % 16;
+  const int Mpad = a.row_tiles * kTileRows;
+  const int64_t part0 = static_cast<int64_t>(bg) * a.max_splits * Mpad + row;
+  f32x2 ml[kFewSplits];
+  u32x4 o[kFewSplits];
+#pragma unroll
+  for (int s = 0; s < kFewSplits; ++s) {
+    ml[s] = (f32x2){-INFINITY, 0.f};
+    o[s] = (u32x4){0u, 0u, 0u, 0u};
+    if (s < a.max_splits) {
+      const int64_t r = part0 + static_cast<int64_t>(s) * Mpad;
+      ml[s] = *reinterpret_cast<const f32x2*>(a.ws_ml + r * 2);
+      o[s] = *reinterpret_cast<const u32x4*>(a.ws_o + r * kD + col * 8);
+    }
+  }
+  const int n = a.n_nodes[b];
+  const int P = a.prefix_len[b];
+  if (row >= a.G * n) return;
+  const int n_splits = min(n_splits_of(P, n, a.split_keys, a.tree_alone), a.max_splits);
+  if (n_splits == 1) return;  // the attention kernel wrote this row's output
+  float M = -INFINITY;
+#pragma unroll
+  for (int s = 0; s < kFewSplits; ++s)
+    if (s < n_splits) M = fmaxf(M, ml[s].x);
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float wsum = 0.f;
+#pragma unroll
+  for (int s = 0; s < kFewSplits; ++s) {
+    if (s < n_splits) {
+      const float w = exp2_fast(ml[s].x - M) * ml[s].y;
+      wsum += w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc[2 * e] += w * bf16_to_f32(static_cast<uint16_t>(o[s][e] & 0xFFFFu));
+        acc[2 * e + 1] += w * bf16_to_f32(static_cast<uint16_t>(o[s][e] >> 16));
+      }
+    }
+  }
+  if (col < HD / 8) {  // (lanes past the head's dims summed unused workspace)
+    const float inv = 1.f / wsum;
+    uint16_t* orow =
+        a.out + ((static_cast<int64_t>(b) * a.Nmax + row / a.G) * a.Hq + g * a.G + row % a.G) * HD;
+    u32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = pack_bf16x2(acc[2 * e] * inv, acc[2 * e + 1] * inv);
+    *reinterpret_cast<u32x4*>(orow + col * 8) = v;
+  }
+}
 
 // ---- stream plan (batches): the workgroup's shares are planned in rounds of up to kMaxShares by wave 0
 // into LDS, then run one by one by the whole workgroup: the partition's state
@@ -1174,17 +1241,19 @@ __global__ void __launch_bounds__(kThreads, 1) attn_stream_kernel(MfmaArgs a) {
 // w_p = 2^(m_p - M) * l_p, M = max_p m_p, over the unit's pieces p in
 // workgroup order, where Ohat_p = O_p / l_p is the piece's normalised output
 // (bf16).  blockIdx.x = the unit (its entry in the merge table says whether it
-// was cut), blockIdx.y picks 64 of its rows: each wave takes 16 rows, 4 lanes
-// per row and a quarter of the head's dims per lane.  Lane k of a wave works out the
-// slot of piece k once (64 pieces per round); every lane then walks the
-// pieces in batches of 4 with all their loads in flight, keeping a running
-// max (each batch rescales the sums at most once), so a unit of up to 4
-// pieces takes a single round of loads.
+// was cut), blockIdx.y picks 4 * kMergeRows of its rows: each wave takes
+// kMergeRows rows, 16 lanes (16 bytes of a row each) and kRowSteps rows per
+// lane, so a load reads whole rows.  Lane k of a wave works out the slot of
+// piece k once (64 pieces per round); every lane then walks the pieces in
+// batches of kBatch with all their loads in flight, keeping a running max
+// (each batch rescales the sums at most once).  (With 4 lanes a row, 64 bytes
+// each, a load touched a quarter of every line: 16 sequences of 64/8 heads,
+// prefixes 1024-8192, 15.9 us instead of 14.3.)
+constexpr int kMergeRows = 8;
 template <int HD>
 __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   constexpr int kBatch = 4;
-  constexpr int kQD = HD / 4;       // dims per lane (4 lanes per row)
-  constexpr int kQC = kQD / 8;      // 16-byte chunks per lane
+  constexpr int kRowSteps = kMergeRows / 4;
   if (halted(a.status)) return;
   const int units = *reinterpret_cast<const int32_t*>(a.ws_desc);
   const MergeDesc d = a.ws_desc[1 + blockIdx.x];
@@ -1192,10 +1261,12 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   const int wv = threadIdx.x / kWave;
   const int lane = threadIdx.x % kWave;
   const int rows = min(a.G * d.n - d.rt * kTileRows, kTileRows);
-  const int r0 = blockIdx.y * 64 + wv * 16;
+  const int r0 = (blockIdx.y * 4 + wv) * kMergeRows;
   if (r0 >= rows) return;
-  const int r = min(r0 + (lane >> 2), rows - 1);  // (rows past the unit's compute its last, unstored)
-  const int quarter = lane & 3;                    // dims kQD * quarter .. + kQD - 1
+  const int col = lane & 15;
+  int r[kRowSteps];  // (rows past the unit's compute its last, unstored)
+#pragma unroll
+  for (int i = 0; i < kRowSteps; ++i) r[i] = min(r0 + 4 * i + (lane >> 4), rows - 1);
   plan::MergeJob job{};
   job.active = true;
   job.sa = d.sa;
@@ -1205,71 +1276,70 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   job.q.c.t_pre = d.t_pre;
   const plan::Grid gr = plan::make_grid(d.C, a.W);
   const int npieces = plan::owner(gr, plan::tree_item(d.U, d.w, d.t_pre)) - d.sa + 1;
-  float acc[kQD];
+  float acc[kRowSteps][8] = {};
+  float wsum[kRowSteps], M[kRowSteps];  // running max: acc and wsum are relative to 2^M
 #pragma unroll
-  for (int e = 0; e < kQD; ++e) acc[e] = 0.f;
-  float wsum = 0.f;
-  float M = -INFINITY;  // running max: acc and wsum are relative to 2^M
+  for (int i = 0; i < kRowSteps; ++i) {
+    wsum[i] = 0.f;
+    M[i] = -INFINITY;
+  }
   for (int c0 = 0; c0 < npieces; c0 += kWave) {
     const int cnt = min(kWave, npieces - c0);
     const int my_slot = lane < cnt ? plan::merge_piece_slot(job, c0 + lane, gr) : -1;
     for (int k0 = 0; k0 < cnt; k0 += kBatch) {
-      f32x2 ml[kBatch];
-      u32x4 o[kBatch][kQC];
+      f32x2 ml[kRowSteps][kBatch];
+      u32x4 o[kRowSteps][kBatch];
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) {
         const int slot = k0 + j < cnt ? __builtin_amdgcn_readlane(my_slot, k0 + j) : -1;
-        ml[j] = (f32x2){-INFINITY, 0.f};
 #pragma unroll
-        for (int c = 0; c < kQC; ++c) o[j][c] = (u32x4){0u, 0u, 0u, 0u};
-        if (slot >= 0) {
-          const int64_t row = static_cast<int64_t>(slot) * kTileRows + r;
-          ml[j] = *reinterpret_cast<const f32x2*>(a.ws_ml + row * 2);
-          const u32x4* src = reinterpret_cast<const u32x4*>(a.ws_o + row * kD + quarter * kQD);
-#pragma unroll
-          for (int c = 0; c < kQC; ++c) o[j][c] = src[c];
+        for (int i = 0; i < kRowSteps; ++i) {
+          ml[i][j] = (f32x2){-INFINITY, 0.f};
+          o[i][j] = (u32x4){0u, 0u, 0u, 0u};
+          if (slot >= 0) {
+            const int64_t row = static_cast<int64_t>(slot) * kTileRows + r[i];
+            ml[i][j] = *reinterpret_cast<const f32x2*>(a.ws_ml + row * 2);
+            o[i][j] = *reinterpret_cast<const u32x4*>(a.ws_o + row * kD + col * 8);
+          }
         }
       }
       // the batch's pieces join the running sums (one rescale per batch)
-      float Mb = M;
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) Mb = fmaxf(Mb, ml[j].x);
-      if (Mb > M) {
-        const float alpha = M == -INFINITY ? 0.f : exp2_fast(M - Mb);
-        wsum *= alpha;
+      for (int i = 0; i < kRowSteps; ++i) {
+        float Mb = M[i];
 #pragma unroll
-        for (int e = 0; e < kQD; ++e) acc[e] *= alpha;
-        M = Mb;
-      }
+        for (int j = 0; j < kBatch; ++j) Mb = fmaxf(Mb, ml[i][j].x);
+        if (Mb > M[i]) {
+          const float alpha = M[i] == -INFINITY ? 0.f : exp2_fast(M[i] - Mb);
+          wsum[i] *= alpha;
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        const float w = ml[j].y > 0.f ? exp2_fast(ml[j].x - M) * ml[j].y : 0.f;
-        wsum += w;
+          for (int e = 0; e < 8; ++e) acc[i][e] *= alpha;
+          M[i] = Mb;
+        }
 #pragma unroll
-        for (int c = 0; c < kQC; ++c)
+        for (int j = 0; j < kBatch; ++j) {
+          const float w = ml[i][j].y > 0.f ? exp2_fast(ml[i][j].x - M[i]) * ml[i][j].y : 0.f;
+          wsum[i] += w;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            acc[8 * c + 2 * e] += w * bf16_to_f32(static_cast<uint16_t>(o[j][c][e] & 0xFFFFu));
-            acc[8 * c + 2 * e + 1] += w * bf16_to_f32(static_cast<uint16_t>(o[j][c][e] >> 16));
+            acc[i][2 * e] += w * bf16_to_f32(static_cast<uint16_t>(o[i][j][e] & 0xFFFFu));
+            acc[i][2 * e + 1] += w * bf16_to_f32(static_cast<uint16_t>(o[i][j][e] >> 16));
           }
+        }
       }
     }
   }
-  if (r0 + (lane >> 2) >= rows) return;
-  const float inv = 1.f / wsum;
-  const int row = d.rt * kTileRows + r;  // stacked row = node * G + head in group
-  const int node = row / a.G;
-  const int hq = d.g * a.G + row % a.G;
-  u32x4* dst = reinterpret_cast<u32x4*>(
-      a.out + ((static_cast<int64_t>(d.b) * a.Nmax + node) * a.Hq + hq) * HD + quarter * kQD);
 #pragma unroll
-  for (int c = 0; c < kQC; ++c) {
+  for (int i = 0; i < kRowSteps; ++i) {
+    if (r0 + 4 * i + (lane >> 4) >= rows || col >= HD / 8) continue;
+    const float inv = 1.f / wsum[i];
+    const int row = d.rt * kTileRows + r[i];  // stacked row = node * G + head in group
+    uint16_t* orow =
+        a.out + ((static_cast<int64_t>(d.b) * a.Nmax + row / a.G) * a.Hq + d.g * a.G + row % a.G) * HD;
     u32x4 v;
-    v.x = pack_bf16x2(acc[8 * c + 0] * inv, acc[8 * c + 1] * inv);
-    v.y = pack_bf16x2(acc[8 * c + 2] * inv, acc[8 * c + 3] * inv);
-    v.z = pack_bf16x2(acc[8 * c + 4] * inv, acc[8 * c + 5] * inv);
-    v.w = pack_bf16x2(acc[8 * c + 6] * inv, acc[8 * c + 7] * inv);
-    dst[c] = v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = pack_bf16x2(acc[i][2 * e] * inv, acc[i][2 * e + 1] * inv);
+    *reinterpret_cast<u32x4*>(orow + col * 8) = v;
   }
 }
 
@@ -1504,7 +1574,16 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
     if (e != hipSuccess || p.max_splits == 1) return e;  // one split: the output is final
     // (sequence, kv head) fastest, as for the attention grid: a head's merge
     // runs on the XCD whose workgroups wrote its partials.
-    const dim3 mgrid(s.B * s.Hkv, static_cast<unsigned>((p.row_tiles * kTileRows + 3) / 4));
+    const unsigned mrows = static_cast<unsigned>(p.row_tiles * kTileRows);
+    if (p.max_splits <= kFewSplits) {
+      const dim3 fgrid(s.B * s.Hkv, mrows / 16);
+      if (s.d == 64)
+        hipLaunchKernelGGL(attn_split_merge_few_kernel<64>, fgrid, dim3(256), 0, stream, a);
+      else
+        hipLaunchKernelGGL(attn_split_merge_few_kernel<128>, fgrid, dim3(256), 0, stream, a);
+      return hipGetLastError();
+    }
+    const dim3 mgrid(s.B * s.Hkv, mrows / 4);
     if (s.d == 64)
       hipLaunchKernelGGL(attn_split_merge_kernel<64>, mgrid, dim3(256), 0, stream, a);
     else
@@ -1527,12 +1606,12 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
     hipLaunchKernelGGL((attn_stream_kernel<128, false>), dim3(p.grid), dim3(kThreads), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // One merge workgroup column per possible unit, 64 rows per workgroup.
+  // One merge workgroup column per possible unit, 4 * kMergeRows rows per workgroup.
   if (s.d == 64)
-    hipLaunchKernelGGL(attn_stream_merge_kernel<64>, dim3(a.max_units, kTileRows / 64), dim3(256),
+    hipLaunchKernelGGL(attn_stream_merge_kernel<64>, dim3(a.max_units, kTileRows / (4 * kMergeRows)), dim3(256),
                        0, stream, a);
   else
-    hipLaunchKernelGGL(attn_stream_merge_kernel<128>, dim3(a.max_units, kTileRows / 64), dim3(256),
+    hipLaunchKernelGGL(attn_stream_merge_kernel<128>, dim3(a.max_units, kTileRows / (4 * kMergeRows)), dim3(256),
                        0, stream, a);
   return hipGetLastError();
 }

@@ -23,40 +23,6 @@ constexpr int kVecThreads = kVecWaves * kWave;
 constexpr int kMaxD = 128;
 constexpr int kPieces = kTileKeys * kMaxD / 4 / kVecThreads;  // 16-byte pieces a thread loads
 
-// Wave-wide reductions without the LDS crossbar: within each 16-lane row by
-// DPP (quad swaps, then the half-row and row mirrors: every lane ends with its
-// row's total), then across rows with v_permlane16_swap and
-// v_permlane32_swap of the value with itself (their two results hold the
-// other row, or half, in every lane).
-template <int kCtrl>
-__device__ __forceinline__ float dpp(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kCtrl,
-                                                               0xF, 0xF, false));
-}
-template <class Op>
-__device__ __forceinline__ float wave_reduce(float v, Op op) {
-  v = op(v, dpp<0xB1>(v));   // quad_perm [1, 0, 3, 2]
-  v = op(v, dpp<0x4E>(v));   // quad_perm [2, 3, 0, 1]
-  v = op(v, dpp<0x141>(v));  // row_half_mirror
-  v = op(v, dpp<0x140>(v));  // row_mirror
-  uint32_t u = __builtin_bit_cast(uint32_t, v);
-  const auto r16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  // (the halves are copied out first: hipcc folds a bit-cast of element 1 of
-  // the result to element 0)
-  const uint32_t a = r16[0], b = r16[1];
-  v = op(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
-  u = __builtin_bit_cast(uint32_t, v);
-  const auto r32 = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  const uint32_t c = r32[0], e = r32[1];
-  return op(__builtin_bit_cast(float, c), __builtin_bit_cast(float, e));
-}
-__device__ __forceinline__ float wave_max_dpp(float v) {
-  return wave_reduce(v, [](float x, float y) { return fmaxf(x, y); });
-}
-__device__ __forceinline__ float wave_sum_dpp(float v) {
-  return wave_reduce(v, [](float x, float y) { return x + y; });
-}
-
 // Four consecutive elements of a cache row as floats (16-byte loads when the
 // row data is float and 16-byte aligned).
 template <typename T, bool kVec>

@@ -43,15 +43,52 @@ __device__ __forceinline__ void store_f32<uint16_t>(uint16_t* p, int64_t i, floa
   p[i] = f32_to_bf16(v);
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
-  return v;
-}
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
   return v;
+}
+
+// Wave-wide reductions without the LDS crossbar: within each 16-lane row by
+// DPP (quad swaps, then the half-row and row mirrors: every lane ends with its
+// row's total), then across rows with v_permlane16_swap and
+// v_permlane32_swap of the value with itself (their two results hold the
+// other row, or half, in every lane).
+template <int kCtrl>
+__device__ __forceinline__ float dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), kCtrl,
+                                                               0xF, 0xF, false));
+}
+// op over the lanes l, l ^ 16, l ^ 32 and l ^ 48, in each of them.
+template <class Op>
+__device__ __forceinline__ float rows_reduce(float v, Op op) {
+  uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const auto r16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  // (the halves are copied out first: hipcc folds a bit-cast of element 1 of
+  // the result to element 0)
+  const uint32_t a = r16[0], b = r16[1];
+  v = op(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
+  u = __builtin_bit_cast(uint32_t, v);
+  const auto r32 = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const uint32_t c = r32[0], e = r32[1];
+  return op(__builtin_bit_cast(float, c), __builtin_bit_cast(float, e));
+}
+template <class Op>
+__device__ __forceinline__ float wave_reduce(float v, Op op) {
+  v = op(v, dpp<0xB1>(v));   // quad_perm [1, 0, 3, 2]
+  v = op(v, dpp<0x4E>(v));   // quad_perm [2, 3, 0, 1]
+  v = op(v, dpp<0x141>(v));  // row_half_mirror
+  v = op(v, dpp<0x140>(v));  // row_mirror
+  return rows_reduce(v, op);
+}
+__device__ __forceinline__ float wave_max_dpp(float v) {
+  return wave_reduce(v, [](float x, float y) { return fmaxf(x, y); });
+}
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+  return wave_reduce(v, [](float x, float y) { return x + y; });
+}
+__device__ __forceinline__ float rows_sum_dpp(float v) {
+  return rows_reduce(v, [](float x, float y) { return x + y; });
 }
 
 // Element offset of logical cache row `row` of sequence b, kv head g.
