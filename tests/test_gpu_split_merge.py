@@ -3,6 +3,7 @@ them (at most 8 splits: 16 lanes a row; more: a wave a row) and of the splits
 the wave kernel requests up front (32) and weights per lane (64)."""
 import numpy as np
 import pytest
+import torch  # noqa: F401  (its HIP runtime is loaded before the library asks for the device)
 
 import gpu_util as U
 import paper_2603_01639_amd as ltd
