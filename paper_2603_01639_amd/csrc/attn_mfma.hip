@@ -106,6 +106,7 @@ struct MfmaArgs {
   uint16_t* out;
   const int32_t* status;
   int B, Nmax, Hq, Hkv, G, kv_rows, max_blocks, max_prefix;
+  uint32_t g_magic;  // node_of's multiplier (0: divide)
   int kv_shift;  // log2(kv_rows) when kv_rows is a power of two, else -1
   int W;  // stream plan: workgroups of the grid (a power of two)
   // split plan: prefix keys per split, splits of the longest sequence, whether
@@ -114,6 +115,15 @@ struct MfmaArgs {
   float scale_log2;
   float lazy_gap;  // kLazyMax / scale_log2: the raw-score margin of the lazy max
 };
+
+// Node of stacked row r: r / G.  With magic = floor(2^31 / G) + 1 the high half
+// of 2 r * magic is exact while r * G < 2^31 (rows are below 256 G); past
+// kMaxMagicG the magic is 0 and the division is done.
+constexpr int kMaxMagicG = 2048;
+__device__ __forceinline__ int node_of(const MfmaArgs& a, int r) {
+  if (a.g_magic == 0) return r / a.G;
+  return static_cast<int>(__umulhi(2u * static_cast<uint32_t>(r), a.g_magic));
+}
 
 // A-row i of a 32-key block reads key sigma(i); accumulator register r of lane
 // half h then holds key 16*h + r.
@@ -228,7 +238,7 @@ struct Smem {
   unsigned char kv[kStages][kTileBytes];
   ShareDesc share[kMaxShares];
   int64_t next_pos;  // where the next planning round resumes
-  int32_t n_share, first;
+  int32_t n_share;
   uint32_t anc[LTD_MAX_NODES][kAncWords];
   int16_t jump[LTD_MAX_NODES];     // jump pointers of the mask build
   int32_t par[LTD_MAX_NODES];      // the tree's parent links (mask build)
@@ -310,7 +320,17 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   // A wave whose 32 rows are all padding only loads tiles and takes part in
   // the barriers.
   const bool active = row0 + wave * 32 < valid_rows;
-  const int qnode = qvalid ? qrow_idx / a.G : 0;
+  const int qnode = qvalid ? node_of(a, qrow_idx) : 0;
+  // Paged caches: this share's block ids are staged in LDS before the first
+  // tile's addresses are formed, so that address generation never waits on a
+  // global load; the first kThreads of them are requested ahead of everything.
+  // (The share's rows are one contiguous logical range: the tree rows follow
+  // the prefix rows directly.)
+  const int first_blk = kPaged ? key_begin / a.kv_rows : 0;
+  const int n_blk = kPaged ? (key_begin + n_pre + n_tree - 1) / a.kv_rows - first_blk + 1 : 0;
+  const int32_t* bt = a.block_table + (kPaged ? static_cast<int64_t>(b) * a.max_blocks + first_blk : 0);
+  int bt_first = 0;
+  if (kPaged && tid < n_blk) bt_first = bt[tid];
   unsigned char* q_lds = &sm.kv[2][0] + wave * (32 * kD * 2);
   if (active) {
 #pragma unroll
@@ -318,8 +338,9 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
       const int R = 4 * j + (lane >> 4);
       const int idx = min(row0 + wave * 32 + R, valid_rows - 1);
       const int lc = (lane & 15) ^ (R & 15);
+      const int node = node_of(a, idx);
       const uint16_t* src = a.q +
-          ((static_cast<int64_t>(b) * a.Nmax + idx / a.G) * a.Hq + g * a.G + idx % a.G) * HD +
+          ((static_cast<int64_t>(b) * a.Nmax + node) * a.Hq + g * a.G + (idx - node * a.G)) * HD +
           (lc & (HD / 8 - 1)) * 8;
       dma16(lds_addr(q_lds + j * 1024), src);
     }
@@ -339,18 +360,11 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(a.k);
   const unsigned char* vbase = reinterpret_cast<const unsigned char*>(a.v);
   constexpr bool paged = kPaged;  // a paged cache (block table) or one contiguous range per (b, g)
-  // Paged caches: this split's block ids are staged in LDS first, so address
-  // generation never waits on a global load.  The split's rows are one
-  // contiguous logical range (for the last split the tree rows follow the
-  // prefix rows directly).
-  int first_blk = 0;
   if (paged) {
-    first_blk = key_begin / a.kv_rows;
-    const int n_blk = (key_begin + n_pre + n_tree - 1) / a.kv_rows - first_blk + 1;
-    const int32_t* bt = a.block_table + static_cast<int64_t>(b) * a.max_blocks + first_blk;
     // (stored as the block's row group of head g, blk * Hkv + g: its first
     // row is that times kv_rows)
-    for (int j = tid; j < n_blk; j += kThreads) sm.blk[j] = bt[j] * a.Hkv + g;
+    if (tid < n_blk) sm.blk[tid] = bt_first * a.Hkv + g;
+    for (int j = tid + kThreads; j < n_blk; j += kThreads) sm.blk[j] = bt[j] * a.Hkv + g;
     __syncthreads();
   }
   auto row_byte = [&](int row) -> int64_t {  // byte offset of logical cache row `row`
@@ -783,8 +797,9 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
       const int r = cidx / kRowChunks, col = cidx % kRowChunks;
       const int row = wrow0 + r;
       if (row < valid_rows) {
+        const int node = node_of(a, row);
         uint16_t* orow =
-            a.out + ((static_cast<int64_t>(b) * a.Nmax + row / a.G) * a.Hq + g * a.G + row % a.G) * HD;
+            a.out + ((static_cast<int64_t>(b) * a.Nmax + node) * a.Hq + g * a.G + (row - node * a.G)) * HD;
         *reinterpret_cast<u32x4*>(orow + col * 8) =
             *reinterpret_cast<const u32x4*>(stage + r * kRowPitch + col * 16);
       }
@@ -817,11 +832,6 @@ __device__ __forceinline__ plan::SeqCost lane_cost(const MfmaArgs& a, int b, int
   return plan::seq_cost(*P, *n, a.G);
 }
 
-__device__ __forceinline__ int64_t shfl_up_i64(int64_t v, int d) {
-  const int lo = __shfl_up(static_cast<int>(v), d, kWave);
-  const int hi = __shfl_up(static_cast<int>(v >> 32), d, kWave);
-  return (static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo);
-}
 __device__ __forceinline__ int64_t readlane_i64(int64_t v, int l) {
   const int lo = __builtin_amdgcn_readlane(static_cast<int>(v), l);
   const int hi = __builtin_amdgcn_readlane(static_cast<int>(v >> 32), l);
@@ -841,15 +851,21 @@ struct Axis {
   int units;  // units of the whole call
 };
 
-// Inclusive prefix sum over the wave.
+// Inclusive prefix sum over the wave: row shifts within each row of 16 lanes,
+// then the row totals broadcast forward (DPP moves, no LDS crossbar).
+template <int kCtrl, int kRows>
+__device__ __forceinline__ int64_t dpp_add_i64(int64_t x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(x), kCtrl, kRows, 0xF, kRows == 0xF);
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(x >> 32), kCtrl, kRows, 0xF, kRows == 0xF);
+  return x + ((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
+}
 __device__ __forceinline__ int64_t wave_scan_i64(int64_t x) {
-  const int lane = __lane_id();
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int64_t y = shfl_up_i64(x, d);
-    if (lane >= d) x += y;
-  }
-  return x;
+  x = dpp_add_i64<0x111, 0xF>(x);  // row_shr:1
+  x = dpp_add_i64<0x112, 0xF>(x);  // row_shr:2
+  x = dpp_add_i64<0x114, 0xF>(x);  // row_shr:4
+  x = dpp_add_i64<0x118, 0xF>(x);  // row_shr:8
+  x = dpp_add_i64<0x142, 0xA>(x);  // row_bcast:15 -> rows 1, 3
+  return dpp_add_i64<0x143, 0xC>(x);  // row_bcast:31 -> rows 2, 3
 }
 
 __device__ Axis axis_load(const MfmaArgs& a) {
@@ -943,9 +959,9 @@ __device__ plan::SeqAt axis_find(const MfmaArgs& a, const Axis& ax, int64_t p) {
 // arithmetic.  Entry i of the table is the call's unit i; the table's header
 // holds the call's unit count (entries past it are left from other calls).
 struct MergeDesc {
-  int32_t active, b, g, rt, n, sa, sa_first, t_pre;
+  int32_t active, b, g, rt, n, sa, pieces, dense;
   int64_t U, C;
-  int32_t w, pad[3];
+  int32_t w, t_pre, pad[2];
 };
 static_assert(sizeof(MergeDesc) == 64, "descriptor layout");
 
@@ -1084,8 +1100,8 @@ __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
   }
   if (grp == 0 && col < HD / 8) {  // (lanes past the head's dims summed unused workspace)
     const float inv = 1.f / wsum;
-    const int node = row / a.G;
-    const int hq = g * a.G + row % a.G;
+    const int node = node_of(a, row);
+    const int hq = g * a.G + (row - node * a.G);
     uint16_t* orow = a.out + ((static_cast<int64_t>(b) * a.Nmax + node) * a.Hq + hq) * HD;
     u32x4 v;
     v.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
@@ -1153,8 +1169,9 @@ __global__ void __launch_bounds__(256) attn_split_merge_few_kernel(MfmaArgs a) {
   }
   if (col < HD / 8) {  // (lanes past the head's dims summed unused workspace)
     const float inv = 1.f / wsum;
+    const int node = node_of(a, row);
     uint16_t* orow =
-        a.out + ((static_cast<int64_t>(b) * a.Nmax + row / a.G) * a.Hq + g * a.G + row % a.G) * HD;
+        a.out + ((static_cast<int64_t>(b) * a.Nmax + node) * a.Hq + g * a.G + (row - node * a.G)) * HD;
     u32x4 v;
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = pack_bf16x2(acc[2 * e] * inv, acc[2 * e + 1] * inv);
@@ -1180,11 +1197,10 @@ __global__ void __launch_bounds__(kThreads, 1) attn_stream_kernel(MfmaArgs a) {
       const plan::Grid gr = plan::make_grid(ax.C, a.W);
       if (blockIdx.x == 0 && round == 0 && threadIdx.x == 0)
         *reinterpret_cast<int32_t*>(a.ws_desc) = ax.units;  // the merge table's header
-      bool first = round == 0 ? true : sm.first != 0;
       const int64_t pos = round == 0 ? plan::range_lo(gr, s) : sm.next_pos;
       int k = 0;
       const int64_t next = plan::walk_shares(
-          s, gr, pos, first, kMaxShares, find,
+          s, gr, pos, kMaxShares, find,
           [&](const plan::SeqAt& q, const plan::Unit& u, int64_t U, const plan::Share& sh,
               bool whole, int slot) {
             const plan::KeyRange keys = plan::share_keys(sh, q.P);
@@ -1202,7 +1218,8 @@ __global__ void __launch_bounds__(kThreads, 1) attn_stream_kernel(MfmaArgs a) {
                 d.rt = u.rt;
                 d.n = q.n;
                 d.sa = job.sa;
-                d.sa_first = job.sa_first;
+                d.pieces = s - job.sa + 1;
+                d.dense = job.dense;
                 d.t_pre = q.c.t_pre;
                 d.U = U;
                 d.C = ax.C;
@@ -1213,7 +1230,6 @@ __global__ void __launch_bounds__(kThreads, 1) attn_stream_kernel(MfmaArgs a) {
           });
       if (threadIdx.x == 0) {
         sm.n_share = k;
-        sm.first = first ? 1 : 0;
         sm.next_pos = next < plan::range_lo(gr, s + 1) ? next : -1;
       }
     }
@@ -1243,10 +1259,9 @@ __global__ void __launch_bounds__(kThreads, 1) attn_stream_kernel(MfmaArgs a) {
 // (bf16).  blockIdx.x = the unit (its entry in the merge table says whether it
 // was cut), blockIdx.y picks 4 * kMergeRows of its rows: each wave takes
 // kMergeRows rows, 16 lanes (16 bytes of a row each) and kRowSteps rows per
-// lane, so a load reads whole rows.  Lane k of a wave works out the slot of
-// piece k once (64 pieces per round); every lane then walks the pieces in
-// batches of kBatch with all their loads in flight, keeping a running max
-// (each batch rescales the sums at most once).  (With 4 lanes a row, 64 bytes
+// lane, so a load reads whole rows.  The pieces come in batches of kBatch with
+// all their loads in flight, under a running max (each batch rescales the
+// sums at most once).  (With 4 lanes a row, 64 bytes
 // each, a load touched a quarter of every line: 16 sequences of 64/8 heads,
 // prefixes 1024-8192, 15.9 us instead of 14.3.)
 constexpr int kMergeRows = 8;
@@ -1267,15 +1282,19 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   int r[kRowSteps];  // (rows past the unit's compute its last, unstored)
 #pragma unroll
   for (int i = 0; i < kRowSteps; ++i) r[i] = min(r0 + 4 * i + (lane >> 4), rows - 1);
-  plan::MergeJob job{};
-  job.active = true;
-  job.sa = d.sa;
-  job.sa_first = d.sa_first != 0;
-  job.U = d.U;
-  job.u.w = d.w;
-  job.q.c.t_pre = d.t_pre;
-  const plan::Grid gr = plan::make_grid(d.C, a.W);
-  const int npieces = plan::owner(gr, plan::tree_item(d.U, d.w, d.t_pre)) - d.sa + 1;
+  const int npieces = d.pieces;
+  // Slot of piece k: its place alone when every range holds an item of the
+  // unit (always, but for calls with fewer items than workgroups).
+  auto slot_of = [&](int k) -> int {
+    if (k >= npieces) return -1;
+    if (d.dense) return plan::dense_piece_slot(d.sa, k);
+    plan::MergeJob job{};
+    job.sa = d.sa;
+    job.U = d.U;
+    job.u.w = d.w;
+    job.q.c.t_pre = d.t_pre;
+    return plan::merge_piece_slot(job, k, plan::make_grid(d.C, a.W));
+  };
   float acc[kRowSteps][8] = {};
   float wsum[kRowSteps], M[kRowSteps];  // running max: acc and wsum are relative to 2^M
 #pragma unroll
@@ -1283,48 +1302,44 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
     wsum[i] = 0.f;
     M[i] = -INFINITY;
   }
-  for (int c0 = 0; c0 < npieces; c0 += kWave) {
-    const int cnt = min(kWave, npieces - c0);
-    const int my_slot = lane < cnt ? plan::merge_piece_slot(job, c0 + lane, gr) : -1;
-    for (int k0 = 0; k0 < cnt; k0 += kBatch) {
-      f32x2 ml[kRowSteps][kBatch];
-      u32x4 o[kRowSteps][kBatch];
+  for (int k0 = 0; k0 < npieces; k0 += kBatch) {
+    f32x2 ml[kRowSteps][kBatch];
+    u32x4 o[kRowSteps][kBatch];
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        const int slot = k0 + j < cnt ? __builtin_amdgcn_readlane(my_slot, k0 + j) : -1;
-#pragma unroll
-        for (int i = 0; i < kRowSteps; ++i) {
-          ml[i][j] = (f32x2){-INFINITY, 0.f};
-          o[i][j] = (u32x4){0u, 0u, 0u, 0u};
-          if (slot >= 0) {
-            const int64_t row = static_cast<int64_t>(slot) * kTileRows + r[i];
-            ml[i][j] = *reinterpret_cast<const f32x2*>(a.ws_ml + row * 2);
-            o[i][j] = *reinterpret_cast<const u32x4*>(a.ws_o + row * kD + col * 8);
-          }
-        }
-      }
-      // the batch's pieces join the running sums (one rescale per batch)
+    for (int j = 0; j < kBatch; ++j) {
+      const int slot = slot_of(k0 + j);
 #pragma unroll
       for (int i = 0; i < kRowSteps; ++i) {
-        float Mb = M[i];
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) Mb = fmaxf(Mb, ml[i][j].x);
-        if (Mb > M[i]) {
-          const float alpha = M[i] == -INFINITY ? 0.f : exp2_fast(M[i] - Mb);
-          wsum[i] *= alpha;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) acc[i][e] *= alpha;
-          M[i] = Mb;
+        ml[i][j] = (f32x2){-INFINITY, 0.f};
+        o[i][j] = (u32x4){0u, 0u, 0u, 0u};
+        if (slot >= 0) {
+          const int64_t row = static_cast<int64_t>(slot) * kTileRows + r[i];
+          ml[i][j] = *reinterpret_cast<const f32x2*>(a.ws_ml + row * 2);
+          o[i][j] = *reinterpret_cast<const u32x4*>(a.ws_o + row * kD + col * 8);
         }
+      }
+    }
+    // the batch's pieces join the running sums (one rescale per batch)
 #pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-          const float w = ml[i][j].y > 0.f ? exp2_fast(ml[i][j].x - M[i]) * ml[i][j].y : 0.f;
-          wsum[i] += w;
+    for (int i = 0; i < kRowSteps; ++i) {
+      float Mb = M[i];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            acc[i][2 * e] += w * bf16_to_f32(static_cast<uint16_t>(o[i][j][e] & 0xFFFFu));
-            acc[i][2 * e + 1] += w * bf16_to_f32(static_cast<uint16_t>(o[i][j][e] >> 16));
-          }
+      for (int j = 0; j < kBatch; ++j) Mb = fmaxf(Mb, ml[i][j].x);
+      if (Mb > M[i]) {
+        const float alpha = M[i] == -INFINITY ? 0.f : exp2_fast(M[i] - Mb);
+        wsum[i] *= alpha;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[i][e] *= alpha;
+        M[i] = Mb;
+      }
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        const float w = ml[i][j].y > 0.f ? exp2_fast(ml[i][j].x - M[i]) * ml[i][j].y : 0.f;
+        wsum[i] += w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[i][2 * e] += w * bf16_to_f32(static_cast<uint16_t>(o[i][j][e] & 0xFFFFu));
+          acc[i][2 * e + 1] += w * bf16_to_f32(static_cast<uint16_t>(o[i][j][e] >> 16));
         }
       }
     }
@@ -1334,8 +1349,9 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
     if (r0 + 4 * i + (lane >> 4) >= rows || col >= HD / 8) continue;
     const float inv = 1.f / wsum[i];
     const int row = d.rt * kTileRows + r[i];  // stacked row = node * G + head in group
+    const int node = node_of(a, row);
     uint16_t* orow =
-        a.out + ((static_cast<int64_t>(d.b) * a.Nmax + row / a.G) * a.Hq + d.g * a.G + row % a.G) * HD;
+        a.out + ((static_cast<int64_t>(d.b) * a.Nmax + node) * a.Hq + d.g * a.G + (row - node * a.G)) * HD;
     u32x4 v;
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = pack_bf16x2(acc[i][2 * e] * inv, acc[i][2 * e + 1] * inv);
@@ -1543,6 +1559,7 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
   a.Hq = s.Hq;
   a.Hkv = s.Hkv;
   a.G = s.Hq / s.Hkv;
+  a.g_magic = a.G <= kMaxMagicG ? (1u << 31) / static_cast<uint32_t>(a.G) + 1u : 0u;
   a.kv_rows = s.kv_rows;
   a.kv_shift = -1;
   for (int k = 0; k < 31; ++k)

@@ -19,9 +19,11 @@
 // position p has floor(p * W / C) == s: a contiguous run of the unit list.
 // Its first and last unit can be cut (shared with neighbours); the units
 // between are whole.  A cut unit's pieces are the consecutive workgroups
-// that own its items; each piece leaves a partial result in slot 2s (the
-// piece is the first unit of workgroup s) or 2s + 1 (its last), and the merge
-// combines them in workgroup order.
+// that own its items; each piece leaves a partial result in slot 2s + 1 (the
+// unit's first piece: its first item is workgroup s's) or 2s (a later piece),
+// and the merge combines them in workgroup order.  (A workgroup has at most
+// one unit that began before it and one that goes on after it, so the slots
+// are distinct, and a piece's slot follows from its place in the unit alone.)
 //
 // Everything here is constexpr, so the same functions run in the kernels and
 // in a plain host build (how the partition is tested without a GPU).
@@ -176,9 +178,8 @@ constexpr KeyRange share_keys(const Share& sh, int P) {
   return KeyRange{b, e - b};
 }
 
-// The partial-result slot of a piece: 2s when the unit is the first one
-// workgroup s owns items of, else 2s + 1.
-constexpr int piece_slot(int s, bool first_unit_of_wg) { return 2 * s + (first_unit_of_wg ? 0 : 1); }
+// The partial-result slot of workgroup s's piece of a unit.
+constexpr int piece_slot(int s, bool first_piece) { return 2 * s + (first_piece ? 1 : 0); }
 
 // A sequence found on the axis: its index, first position, prefix length,
 // node count and cost data.  `Find` callables map an axis position p
@@ -206,12 +207,10 @@ constexpr int64_t tree_item(int64_t U, int w, int t_pre) {
 // or where an earlier call stopped): visit(seq, unit, U, share, whole, slot)
 // for up to `limit` units it owns items of.  U is the unit's axis start,
 // `whole` says the share is the entire unit (its output is final), `slot` is
-// where a partial share leaves its result; `first` tracks whether a share was
-// visited yet.  Returns the position to resume from, at or past the range's
-// end once every share was visited.
+// where a partial share leaves its result.  Returns the position to resume
+// from, at or past the range's end once every share was visited.
 template <class Find, class Visit>
-constexpr int64_t walk_shares(int s, const Grid& gr, int64_t pos, bool& first, int limit, Find find,
-                              Visit visit) {
+constexpr int64_t walk_shares(int s, const Grid& gr, int64_t pos, int limit, Find find, Visit visit) {
   const int64_t lo = range_lo(gr, s);
   const int64_t hi = range_lo(gr, s + 1);
   int visited = 0;
@@ -221,8 +220,8 @@ constexpr int64_t walk_shares(int s, const Grid& gr, int64_t pos, bool& first, i
     const int64_t U = q.pre + u.start;
     const Share sh = share_of(U, u.w, q.c.t_pre, lo, hi);
     if (!sh.empty()) {
-      visit(q, u, U, sh, first_item(U, u.w) >= lo && sh.j0 == 0 && sh.tree, piece_slot(s, first));
-      first = false;
+      const bool begins = first_item(U, u.w) >= lo;  // the unit's first item is this workgroup's
+      visit(q, u, U, sh, begins && sh.j0 == 0 && sh.tree, piece_slot(s, begins));
       ++visited;
     }
     pos = unit_end(q, u);
@@ -232,10 +231,9 @@ constexpr int64_t walk_shares(int s, const Grid& gr, int64_t pos, bool& first, i
 
 template <class Find, class Visit>
 constexpr void for_each_share(int s, const Grid& gr, Find find, Visit visit) {
-  bool first = true;
   int64_t pos = range_lo(gr, s);
   const int64_t hi = range_lo(gr, s + 1);
-  while (pos < hi) pos = walk_shares(s, gr, pos, first, 1 << 30, find, visit);
+  while (pos < hi) pos = walk_shares(s, gr, pos, 1 << 30, find, visit);
 }
 
 // The merge of a unit, worked out by the workgroup s that owns the unit's tree
@@ -249,37 +247,36 @@ struct MergeJob {
   Unit u;
   int64_t U;
   int sa;
-  bool sa_first;  // the unit is the first one workgroup sa owns items of
+  // Every range is at least a tile weight long, so each of the workgroups
+  // sa .. s owns an item of the unit (they are exactly its pieces).
+  bool dense;
 };
 
+// (`find` is not called: a unit's slots follow from its pieces' places in it.)
 template <class Find>
 constexpr MergeJob unit_job(const SeqAt& q, const Unit& u, int64_t U, int s, const Grid& gr,
-                            Find find) {
+                            const Find&) {
   MergeJob j{};
   j.q = q;
   j.u = u;
   j.U = U;
-  j.sa = owner(gr, first_item(U, u.w));
-  j.active = j.sa != s;
-  j.sa_first = false;
-  if (!j.active) return j;
-  // Is u the first unit workgroup sa owns items of?  Yes when sa's first
-  // position is in u, or lies past the last item of the unit just before u.
-  const int64_t lo_a = range_lo(gr, j.sa);
-  const SeqAt qa = find(lo_a);
-  const Unit ua = locate(lo_a - qa.pre, qa.c);
-  const int64_t Ua = qa.pre + ua.start;
-  j.sa_first = Ua == U || (lo_a > tree_item(Ua, ua.w, qa.c.t_pre) && unit_end(qa, ua) == U);
+  const int64_t I = first_item(U, u.w);
+  j.active = I < range_lo(gr, s);
+  j.sa = j.active ? owner(gr, I) : s;
+  j.dense = gr.q >= u.w;
   return j;
 }
 
 // The slot of piece k (workgroup sa + k) of a merge job, or -1 when that
 // workgroup owns no item of the unit (its range fell between two items).
+constexpr int dense_piece_slot(int sa, int k) { return piece_slot(sa + k, k == 0); }
 constexpr int merge_piece_slot(const MergeJob& j, int k, const Grid& gr) {
-  const int sp = j.sa + k;
-  const Share sh = share_of(j.U, j.u.w, j.q.c.t_pre, range_lo(gr, sp), range_lo(gr, sp + 1));
-  if (sh.empty()) return -1;
-  return piece_slot(sp, k > 0 || j.sa_first);
+  if (!j.dense) {
+    const int sp = j.sa + k;
+    const Share sh = share_of(j.U, j.u.w, j.q.c.t_pre, range_lo(gr, sp), range_lo(gr, sp + 1));
+    if (sh.empty()) return -1;
+  }
+  return dense_piece_slot(j.sa, k);
 }
 
 }  // namespace plan
