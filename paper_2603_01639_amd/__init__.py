@@ -121,19 +121,24 @@ def _p(t) -> Optional[int]:
 
 
 def _stream(stream) -> Optional[int]:
+    if stream is not None:
+        return stream.cuda_stream
+    # The current stream's handle without a torch.cuda.Stream object around it:
+    # building one took 2.9 of a call's 12.1 us of host time (a drafting phase
+    # of 12 calls and 25 launches is bound by the host: 148.7 us with it, 123.2
+    # without).
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dtype_code(t) -> int:
     import torch
-    if t.dtype == torch.float32:
-        return DTYPE_F32
-    if t.dtype == torch.bfloat16:
+    dtype = t.dtype
+    if dtype == torch.bfloat16:
         return DTYPE_BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    if dtype == torch.float32:
+        return DTYPE_F32
+    raise TypeError(f"unsupported dtype {dtype}")
 
 
 def _check(fn, rc):
