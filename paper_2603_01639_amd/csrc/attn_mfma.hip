@@ -37,7 +37,7 @@
 // c ^ 4*(k & 3)); the V^T operand comes from ds_read_b64_tr_b16 transpose
 // reads, two per MFMA.
 //
-// The ancestor sets of the tree split are built in LDS as N x 256-bit masks by
+// The ancestor sets of the tree split are built in LDS as 256-bit masks by
 // pointer doubling over the parent links: anc(i) = anc(i) | anc(jump(i)),
 // jump(i) = jump(jump(i)), ceil(log2(depth + 1)) <= 8 rounds for N <= 256.
 //
@@ -239,9 +239,8 @@ struct Smem {
   ShareDesc share[kMaxShares];
   int64_t next_pos;  // where the next planning round resumes
   int32_t n_share;
-  uint32_t anc[LTD_MAX_NODES][kAncWords];
-  int16_t jump[LTD_MAX_NODES];     // jump pointers of the mask build
-  int32_t par[LTD_MAX_NODES];      // the tree's parent links (mask build)
+  uint32_t anc[kAncWords][LTD_MAX_NODES];  // word w of every node's ancestor set
+  int32_t par[kWaves][LTD_MAX_NODES];  // each wave's parent links, then its jump pointers (mask build)
   int32_t blk[kMaxSplitBlocks];  // physical block ids of this split's rows (paged)
 };
 // The Q rows are loaded into ring slots 2 and 3 (8 KiB per wave) before the
@@ -347,11 +346,13 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   }
   constexpr int kNodesPerLane = LTD_MAX_NODES / kWave;
   const int nslots = (n + kWave - 1) / kWave;  // node slots holding a node of this tree
-  if (kTree && wave == 0) {
+  const bool builds_mask = kTree && 32 * wave < n;  // this wave's 32 nodes are in the tree
+  int32_t* jump = sm.par[wave];
+  if (builds_mask) {
 #pragma unroll
     for (int k = 0; k < kNodesPerLane; ++k)
       if (k < nslots)
-        dma4(lds_addr(&sm.par[kWave * k]),
+        dma4(lds_addr(jump + kWave * k),
              a.parents + static_cast<int64_t>(b) * a.Nmax + min(lane + kWave * k, n - 1));
   }
 
@@ -486,42 +487,35 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 
-  // The tree's parent links, for wave 0 (lane l handles nodes l + 64*k).
-  int my_parent[kNodesPerLane];
-#pragma unroll
-  for (int k = 0; k < kNodesPerLane; ++k) {
-    const int i = lane + kWave * k;
-    my_parent[k] = -1;
-    if (kTree && wave == 0 && i > 0 && i < n) my_parent[k] = sm.par[i];
-  }
-
-  // ---- ancestor masks (tree split): wave 0 builds them by pointer doubling
-  // over the parent links, anc(i) |= anc(jump(i)), jump(i) = jump(jump(i)).
-  // Each lane keeps the sets and jump pointers of its nodes (i = lane + 64*k)
+  // ---- ancestor masks (tree split) by pointer doubling over the parent
+  // links, anc(i) |= anc(jump(i)), jump(i) = jump(jump(i)).  Wave w builds
+  // word w of every node's set (whether nodes 32w .. 32w + 31 are in it) with
+  // its own copy of the jump pointers, so the waves need no barrier between
+  // rounds.  Each lane keeps its nodes' (i = lane + 64*k) word and jump pointer
   // in registers; a round publishes them to LDS, orders the wave's LDS
   // traffic with one wave-level fence, and reads the jump targets' entries.
   // The rounds stop once every jump pointer has passed the root (after
-  // ceil(log2(depth + 1)) rounds).  The other waves go on to the tile loop,
-  // whose first barrier publishes the masks.
-  if (kTree && wave == 0) {
-    typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
-    u32x8 anc_r[kNodesPerLane];
+  // ceil(log2(depth + 1)) rounds).  The loop's first barrier publishes the
+  // masks; words past the tree's nodes are never used (mask_scores drops keys
+  // past n).
+  if (builds_mask) {
+    uint32_t anc_r[kNodesPerLane];
     int jmp[kNodesPerLane];
 #pragma unroll
     for (int k = 0; k < kNodesPerLane; ++k) {
       const int i = lane + kWave * k;
-#pragma unroll
-      for (int w = 0; w < kAncWords; ++w) anc_r[k][w] = (i < n && (i >> 5) == w) ? (1u << (i & 31)) : 0u;
-      jmp[k] = my_parent[k];
+      anc_r[k] = (i < n && (i >> 5) == wave) ? (1u << (i & 31)) : 0u;
+      jmp[k] = -1;
+      if (i > 0 && i < n) jmp[k] = jump[i];
     }
-    u32x8* anc_lds = reinterpret_cast<u32x8*>(&sm.anc[0][0]);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     for (int r = 0; r < 8; ++r) {
 #pragma unroll
       for (int k = 0; k < kNodesPerLane; ++k) {
         if (k < nslots) {
           const int i = lane + kWave * k;
-          anc_lds[i] = anc_r[k];
-          sm.jump[i] = static_cast<int16_t>(jmp[k]);
+          sm.anc[wave][i] = anc_r[k];
+          jump[i] = jmp[k];
         }
       }
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -530,9 +524,9 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
       for (int k = 0; k < kNodesPerLane; ++k) {
         if (k < nslots) {
           const int j = jmp[k];
-          const int jc = j >= 0 ? j : 0;
-          const u32x8 other = anc_lds[jc];
-          const int jj = sm.jump[jc];
+          const int jc = min(max(j, 0), LTD_MAX_NODES - 1);  // (a malformed link stays in the table)
+          const uint32_t other = sm.anc[wave][jc];
+          const int jj = jump[jc];
           if (j >= 0) {
             anc_r[k] |= other;
             jmp[k] = jj;
@@ -546,7 +540,7 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
 #pragma unroll
     for (int k = 0; k < kNodesPerLane; ++k) {
       const int i = lane + kWave * k;
-      if (i < n) anc_lds[i] = anc_r[k];
+      if (i < n) sm.anc[wave][i] = anc_r[k];
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   }
@@ -613,7 +607,7 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
         const int kfirst = kb * 32 + 16 * h;  // tile key of register r = kfirst + r
         uint32_t vis = 0xFFFFu;
         if (kfirst + 16 > tr.left) vis = (kfirst >= tr.left) ? 0u : ((1u << (tr.left - kfirst)) - 1u);
-        if (tr.tree) vis &= (sm.anc[qnode][(tr.rel + kb * 32) >> 5] >> (16 * h)) & 0xFFFFu;
+        if (tr.tree) vis &= (sm.anc[(tr.rel + kb * 32) >> 5][qnode] >> (16 * h)) & 0xFFFFu;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           if (!((vis >> r) & 1u)) s[kb][r] = -INFINITY;
