@@ -84,6 +84,8 @@ constexpr int kKLoads = kLoadsPerTile / 2;  // K (and V) chunks per lane per til
 constexpr float kLazyMax = 8.f;
 constexpr float kNoMax = -__FLT_MAX__;  // running max before any key (raw score units)
 constexpr int kStages = 4;                // K/V tiles in the LDS ring
+constexpr int kSchedMfma = 0x008, kSchedDsRead = 0x100;  // sched_group_barrier classes
+constexpr int kKAhead = 2;                // k-steps of K fragments in flight
 constexpr int kMaxSplitTiles = 32;        // split plan: longest split in key tiles
 constexpr int kMaxMergeSplits = 1024;     // split plan: splits the merge takes at most
 constexpr int kTileRows = kWaves * 32;    // stacked query rows per workgroup (one unit)
@@ -106,7 +108,8 @@ struct MfmaArgs {
   uint16_t* out;
   const int32_t* status;
   int B, Nmax, Hq, Hkv, G, kv_rows, max_blocks, max_prefix;
-  uint32_t g_magic;  // node_of's multiplier (0: divide)
+  uint32_t g_magic;  // node_of's multiplier and shift
+  int g_shift;
   int kv_shift;  // log2(kv_rows) when kv_rows is a power of two, else -1
   int W;  // stream plan: workgroups of the grid (a power of two)
   // split plan: prefix keys per split, splits of the longest sequence, whether
@@ -116,13 +119,10 @@ struct MfmaArgs {
   float lazy_gap;  // kLazyMax / scale_log2: the raw-score margin of the lazy max
 };
 
-// Node of stacked row r: r / G.  With magic = floor(2^31 / G) + 1 the high half
-// of 2 r * magic is exact while r * G < 2^31 (rows are below 256 G); past
-// kMaxMagicG the magic is 0 and the division is done.
-constexpr int kMaxMagicG = 2048;
+// Node of stacked row r: r / G, by a multiplication.  With G <= 2^shift and
+// magic = floor(2^(31 + shift) / G) + 1 it is exact for every r below 2^31.
 __device__ __forceinline__ int node_of(const MfmaArgs& a, int r) {
-  if (a.g_magic == 0) return r / a.G;
-  return static_cast<int>(__umulhi(2u * static_cast<uint32_t>(r), a.g_magic));
+  return static_cast<int>(__umulhi(2u * static_cast<uint32_t>(r), a.g_magic) >> a.g_shift);
 }
 
 // A-row i of a 32-key block reads key sigma(i); accumulator register r of lane
@@ -592,6 +592,15 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
         s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kb][kk], qf[kk], s[kb], 0, 0, 0);
+    // The K fragments are read kKAhead k-steps before their MFMAs (left alone,
+    // the compiler reads each step's right before it and waits for LDS).
+    __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2 * kKAhead, 0);
+#pragma unroll
+    for (int kk = 0; kk < HD / 16 - kKAhead; ++kk) {
+      __builtin_amdgcn_sched_group_barrier(kSchedMfma, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(kSchedMfma, 2 * kKAhead, 0);
   };
 
   // The online softmax of a tile in three parts: the key mask (tiles that
@@ -1553,7 +1562,8 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
   a.Hq = s.Hq;
   a.Hkv = s.Hkv;
   a.G = s.Hq / s.Hkv;
-  a.g_magic = a.G <= kMaxMagicG ? (1u << 31) / static_cast<uint32_t>(a.G) + 1u : 0u;
+  while ((int64_t{1} << a.g_shift) < a.G) ++a.g_shift;
+  a.g_magic = static_cast<uint32_t>((uint64_t{1} << (31 + a.g_shift)) / a.G + 1);
   a.kv_rows = s.kv_rows;
   a.kv_shift = -1;
   for (int k = 0; k < 31; ++k)

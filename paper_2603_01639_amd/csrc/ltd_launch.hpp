@@ -28,6 +28,7 @@ struct AttnPlan {
   int split_keys;    // split plan: prefix keys per split (a multiple of the key tile)
   int max_splits;    // split plan: splits of the longest sequence
   int row_tiles;     // split plan: row tiles per (sequence, kv head)
+  int tile_rows;     // split plan: stacked rows of a row tile
   bool tree_alone;   // split plan: the tree's keys may take a split of their own
   size_t workspace_bytes;
 };

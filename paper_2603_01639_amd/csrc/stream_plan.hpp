@@ -210,7 +210,7 @@ constexpr int64_t tree_item(int64_t U, int w, int t_pre) {
 // where a partial share leaves its result.  Returns the position to resume
 // from, at or past the range's end once every share was visited.
 template <class Find, class Visit>
-constexpr int64_t walk_shares(int s, const Grid& gr, int64_t pos, int limit, Find find, Visit visit) {
+__attribute__((always_inline)) constexpr int64_t walk_shares(int s, const Grid& gr, int64_t pos, int limit, Find find, Visit visit) {
   const int64_t lo = range_lo(gr, s);
   const int64_t hi = range_lo(gr, s + 1);
   int visited = 0;
