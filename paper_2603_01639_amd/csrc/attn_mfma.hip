@@ -48,6 +48,7 @@
 // 2 dim blocks for O^T, half the MFMAs of a tile.  Partial results keep the
 // 128-dim row pitch in the workspace.
 #include <algorithm>
+#include <type_traits>
 
 #include "ltd_device.hpp"
 #include "ltd_launch.hpp"
@@ -115,6 +116,7 @@ struct MfmaArgs {
   // split plan: prefix keys per split, splits of the longest sequence, whether
   // the tree may take a split of its own, row tiles per (sequence, kv head)
   int split_keys, max_splits, tree_alone, row_tiles;
+  int tile_rows;  // stacked rows per unit
   float scale_log2;
   float lazy_gap;  // kLazyMax / scale_log2: the raw-score margin of the lazy max
 };
@@ -279,7 +281,14 @@ __device__ __forceinline__ LoadPlan make_load_plan(int wave, int lane) {
 // The cache layout (kPaged) is a compile-time choice, so each kernel's tile
 // loop keeps only its own layout's addressing state in scalar registers (the
 // contiguous instantiation of the split kernel then spills none of them).
-template <bool kTree, int HD, bool kPaged>
+// kKG is the number of key groups.  With one, wave w takes rows 32w .. 32w + 31
+// of the unit and all 64 keys of a tile.  With two (units of at most 128 rows),
+// waves 2r and 2r + 1 take rows 32r .. 32r + 31 and one 32-key half of every
+// tile each, and the pair's results are joined through LDS at the end: all 8
+// waves then work where half of them would only load tiles (32/8 heads, prefix
+// 1196, 12 nodes, ten layers and acceptance 118.1 -> 115.7 us; 64/8 heads,
+// prefix 4096, 8 nodes 12.8 -> 12.0; 11 sequences of 56 rows 43.0 -> 42.0).
+template <bool kTree, int HD, bool kPaged, int kKG>
 __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g, int row0,
                                        int valid_rows, int key_begin, int n_pre, int P, int n,
                                        bool final_out, int slot) {
@@ -292,6 +301,9 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   const int lane = tid % kWave;
   const int h = lane >> 5;
   const int l32 = lane & 31;
+  constexpr int kKB = 2 / kKG;  // 32-key blocks of a tile that a wave takes
+  const int rb = wave / kKG;    // the wave's block of 32 rows
+  const int kg = kKG == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave % kKG);  // and its first key block
   const int n_tree = kTree ? n : 0;  // keys of the second range
   const int tA = (n_pre + kKT - 1) / kKT;
   const int n_tiles = tA + (n_tree + kKT - 1) / kKT;
@@ -314,11 +326,11 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   // 256*R in its 8 KiB block, with 16-byte chunk c at c ^ (R & 15), the
   // layout the K operand also uses; rows past valid_rows repeat the last
   // valid row (their results are never stored).
-  const int qrow_idx = row0 + wave * 32 + l32;
+  const int qrow_idx = row0 + rb * 32 + l32;
   const bool qvalid = qrow_idx < valid_rows;
   // A wave whose 32 rows are all padding only loads tiles and takes part in
   // the barriers.
-  const bool active = row0 + wave * 32 < valid_rows;
+  const bool active = row0 + rb * 32 < valid_rows;
   const int qnode = qvalid ? node_of(a, qrow_idx) : 0;
   // Paged caches: this share's block ids are staged in LDS before the first
   // tile's addresses are formed, so that address generation never waits on a
@@ -335,7 +347,7 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int R = 4 * j + (lane >> 4);
-      const int idx = min(row0 + wave * 32 + R, valid_rows - 1);
+      const int idx = min(row0 + rb * 32 + R, valid_rows - 1);
       const int lc = (lane & 15) ^ (R & 15);
       const int node = node_of(a, idx);
       const uint16_t* src = a.q +
@@ -463,9 +475,8 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   };
 
   // The first tiles, behind Q.
-#pragma unroll
-  for (int t = 0; t < kStages - 2; ++t)
-    if (t < n_tiles) issue_tile(t);
+#pragma unroll 1
+  for (int t = 0; t < min(kStages - 2, n_tiles); ++t) issue_tile(t);
   // This wave's Q rows and parent links have landed once no more than the
   // tiles' loads are outstanding.
   if (n_tiles >= 2)
@@ -561,7 +572,7 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   int k_rd[HD / 16];
 #pragma unroll
   for (int kk = 0; kk < HD / 16; ++kk)
-    k_rd[kk] = l32 * (kD * 2) + (((2 * kk + h) ^ (l32 & 15)) << 4);
+    k_rd[kk] = (32 * kg + l32) * (kD * 2) + (((2 * kk + h) ^ (l32 & 15)) << 4);
   //  V^T operand: 16-lane group q reads key 16*(q/2) + s/4 (+ the k-step's
   //  base, a multiple of 4), dims 32*db + 16*(q%2) + 4*(s%4).
   const int tr_q = lane >> 4, tr_s = lane & 15;
@@ -570,37 +581,38 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
 #pragma unroll
   for (int db = 0; db < HD / 32; ++db) {
     const int dim = 32 * db + 16 * (tr_q & 1) + 4 * (tr_s & 3);
-    v_rd[db] = tr_key * (kD * 2) + (((dim >> 3) ^ swz_v(tr_key)) << 4) + (dim & 7) * 2;
+    v_rd[db] = (32 * kg + tr_key) * (kD * 2) + (((dim >> 3) ^ swz_v(tr_key)) << 4) + (dim & 7) * 2;
   }
 
   // K fragments of a tile (A operand of S^T), read into registers one phase
   // ahead of their MFMAs.
-  bf16x8 af[2][HD / 16];
+  bf16x8 af[kKB][HD / 16];
   auto load_k = [&](int t) {
     const unsigned char* k_s = sm.kv[t % kStages];
 #pragma unroll
     for (int kk = 0; kk < HD / 16; ++kk)
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < kKB; ++kb)
         af[kb][kk] = *reinterpret_cast<const bf16x8*>(k_s + kb * 32 * (kD * 2) + k_rd[kk]);
   };
   // S^T = K Q^T from the fragments in af, the two 32-key blocks interleaved.
-  auto scores = [&](f32x16(&s)[2]) {
-    s[0] = s[1] = f32x16{};
+  auto scores = [&](f32x16(&s)[kKB]) {
+#pragma unroll
+    for (int kb = 0; kb < kKB; ++kb) s[kb] = f32x16{};
 #pragma unroll
     for (int kk = 0; kk < HD / 16; ++kk)
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < kKB; ++kb)
         s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kb][kk], qf[kk], s[kb], 0, 0, 0);
     // The K fragments are read kKAhead k-steps before their MFMAs (left alone,
     // the compiler reads each step's right before it and waits for LDS).
-    __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2 * kKAhead, 0);
+    __builtin_amdgcn_sched_group_barrier(kSchedDsRead, kKB * kKAhead, 0);
 #pragma unroll
     for (int kk = 0; kk < HD / 16 - kKAhead; ++kk) {
-      __builtin_amdgcn_sched_group_barrier(kSchedMfma, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(kSchedMfma, kKB, 0);
+      __builtin_amdgcn_sched_group_barrier(kSchedDsRead, kKB, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(kSchedMfma, 2 * kKAhead, 0);
+    __builtin_amdgcn_sched_group_barrier(kSchedMfma, kKB * kKAhead, 0);
   };
 
   // The online softmax of a tile in three parts: the key mask (tiles that
@@ -608,15 +620,15 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   // fragments; the reference max m moves only when a score exceeds it by
   // 2^kLazyMax) and the finish, which rescales O and l when some lane's m
   // moved.  The finish must come after the previous tile's P.V product.
-  auto mask_scores = [&](int t, f32x16(&s)[2]) {
+  auto mask_scores = [&](int t, f32x16(&s)[kKB]) {
     const TileRef tr = tile_ref(t);
     if (tr.tree || tr.left < kKT) {
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        const int kfirst = kb * 32 + 16 * h;  // tile key of register r = kfirst + r
+      for (int kb = 0; kb < kKB; ++kb) {
+        const int kfirst = (kg + kb) * 32 + 16 * h;  // tile key of register r = kfirst + r
         uint32_t vis = 0xFFFFu;
         if (kfirst + 16 > tr.left) vis = (kfirst >= tr.left) ? 0u : ((1u << (tr.left - kfirst)) - 1u);
-        if (tr.tree) vis &= (sm.anc[(tr.rel + kb * 32) >> 5][qnode] >> (16 * h)) & 0xFFFFu;
+        if (tr.tree) vis &= (sm.anc[(tr.rel >> 5) + kg + kb][qnode] >> (16 * h)) & 0xFFFFu;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           if (!((vis >> r) & 1u)) s[kb][r] = -INFINITY;
@@ -624,24 +636,28 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
     }
   };
   float m_new = kNoMax, psum = 0.f;
-  auto exponentials = [&](f32x16(&s)[2], bf16x8(&pf)[2][2]) {
+  auto exponentials = [&](f32x16(&s)[kKB], bf16x8(&pf)[kKB][2]) {
     // IEEE maximum (NaN-propagating) needs no operand canonicalisation and
     // maps to three-input v_maximum3_f32.
     float tmax = __builtin_elementwise_maximum(s[0][0], s[0][1]);
 #pragma unroll
-    for (int r = 2; r < 32; r += 2)
+    for (int r = 2; r < 16 * kKB; r += 2)
       tmax = __builtin_elementwise_maximum(__builtin_elementwise_maximum(tmax, s[r >> 4][r & 15]),
                                            s[r >> 4][(r & 15) + 1]);
     tmax = max_xor32(tmax);
     // (scale > 0, so the lazy test can run on raw scores)
     m_new = tmax > m_run + a.lazy_gap ? tmax : m_run;
-    const float neg = -m_new * c;
+    float neg = -m_new * c;
+    // (a key group can go without a visible key for its first tiles: m_new is
+    // still kNoMax there, and a scale above ln 2 would make this infinite and
+    // the masked scores' exponent NaN)
+    if constexpr (kKG == 2) neg = fminf(neg, __FLT_MAX__);
     // The row sum adds the rounded bf16 probabilities, two per
     // v_dot2_f32_bf16 with ones: the very weights P.V multiplies.
     const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3F803F80u);
     float ps = 0.f;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    for (int kb = 0; kb < kKB; ++kb) {
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
         u32x4 pk;
@@ -673,10 +689,10 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
 
   // O^T += V^T P^T for tile t; k-step kc = 2*kb + kk covers keys 32*kb +
   // 16*h + 8*kk .. +7, read as two transposed 4-key reads.
-  auto accumulate = [&](int t, const bf16x8(&pf)[2][2]) {
+  auto accumulate = [&](int t, const bf16x8(&pf)[kKB][2]) {
     const unsigned char* v_s = sm.kv[t % kStages] + kKBytes;
 #pragma unroll
-    for (int kc = 0; kc < 4; ++kc) {
+    for (int kc = 0; kc < 2 * kKB; ++kc) {
       const int koff = (32 * (kc >> 1) + 8 * (kc & 1)) * (kD * 2);
       bf16x8 vf[HD / 32];
 #pragma unroll
@@ -708,9 +724,9 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   };
   // The P^T fragments alternate between two register sets (the loop is
   // unrolled by two), so tile t-1's are never copied.
-  f32x16 s_acc[2];
-  bf16x8 pfa[2][2], pfb[2][2];
-  auto body = [&](int t, const bf16x8(&pf_prev)[2][2], bf16x8(&pf)[2][2]) {
+  f32x16 s_acc[kKB];
+  bf16x8 pfa[kKB][2], pfb[kKB][2];
+  auto body = [&](int t, const bf16x8(&pf_prev)[kKB][2], bf16x8(&pf)[kKB][2]) {
     publish(t);
     if (active) {
       load_k(t);
@@ -721,7 +737,7 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
       // (pins P and its row sum ahead of the rescale branch: otherwise the
       // compiler sinks the exponentials past it, out of reach of the P.V
       // MFMAs they can overlap)
-      asm volatile("" : "+v"(pf[0][0]), "+v"(pf[0][1]), "+v"(pf[1][0]), "+v"(pf[1][1]), "+v"(psum));
+      asm volatile("" : "+v"(pf[0][0]), "+v"(pf[0][1]), "+v"(pf[kKB - 1][0]), "+v"(pf[kKB - 1][1]), "+v"(psum));
       finish_softmax();            // after P.V(t-1): may rescale O
     }
   };
@@ -757,12 +773,47 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   // this XCD's L2 only lengthens the write-back at the end of the kernel.
   constexpr int kRowPitch = kD * 2 + 16;  // padded LDS row (bank spread)
   static_assert(kWaves * 32 * kRowPitch <= kStages * kTileBytes, "staging fits the ring");
-  const int64_t part = static_cast<int64_t>(slot) * kTileRows - row0;  // + absolute row
+  const int64_t part = static_cast<int64_t>(slot) * a.tile_rows - row0;  // + absolute row
   barrier_only();  // every wave is done with the K/V ring; reuse it for staging
+  float lsum = l_run + xor32(l_run);
+  if constexpr (kKG == 2) {
+    // The pair's odd wave hands its max, sum and O to the even one: 16 KiB a
+    // pair, register by register, in the ring's upper half (the row staging
+    // below stays in the lower half).
+    float* xch = reinterpret_cast<float*>(&sm.kv[kStages / 2][0]) + rb * (HD / 32 * 16 * kWave);
+    float* xml = reinterpret_cast<float*>(&sm.kv[kStages / 2 - 1][kKBytes]) + rb * (2 * kWave);
+    static_assert(kWaves / 2 * 32 * kRowPitch <= (kStages / 2 - 1) * kTileBytes + kKBytes, "staging below");
+    if (active && kg == 1) {
+#pragma unroll
+      for (int db = 0; db < HD / 32; ++db)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const f32x4 v = {o_acc[db][4 * j], o_acc[db][4 * j + 1], o_acc[db][4 * j + 2], o_acc[db][4 * j + 3]};
+          reinterpret_cast<f32x4*>(xch)[(db * 4 + j) * kWave + lane] = v;
+        }
+      xml[lane] = m_run;
+      xml[kWave + lane] = lsum;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    barrier_only();
+    if (!active || kg == 1) return;
+    const float m1 = xml[lane], l1 = xml[kWave + lane];
+    const float M = fmaxf(m_run, m1);
+    const float a0 = exp2_fast((m_run - M) * c), a1 = exp2_fast((m1 - M) * c);
+    lsum = lsum * a0 + l1 * a1;
+    m_run = M;
+#pragma unroll
+    for (int db = 0; db < HD / 32; ++db)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 v = reinterpret_cast<const f32x4*>(xch)[(db * 4 + j) * kWave + lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o_acc[db][4 * j + e] = o_acc[db][4 * j + e] * a0 + v[e] * a1;
+      }
+  }
   if (!active) return;
-  unsigned char* stage = &sm.kv[0][0] + wave * (32 * kRowPitch);  // spans ring slots
+  unsigned char* stage = &sm.kv[0][0] + rb * (32 * kRowPitch);  // spans ring slots
   {
-    const float lsum = l_run + xor32(l_run);
     if (!final_out && qvalid && h == 0) {
       f32x2 ml = {lsum > 0.f ? m_run * c : -INFINITY, lsum};
       __builtin_nontemporal_store(ml, reinterpret_cast<f32x2*>(a.ws_ml + (part + qrow_idx) * 2));
@@ -786,7 +837,7 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   constexpr int kRowChunks = HD * 2 / 16;       // 16-byte chunks of an output row
   constexpr int kChunks = 32 * kRowChunks;       // ... of this wave's rows
   static_assert(kChunks % kWave == 0, "whole store rounds");
-  const int wrow0 = row0 + wave * 32;
+  const int wrow0 = row0 + rb * 32;
   // (an opaque copy of the lane index: otherwise the compiler shares the
   // chunk indices below with the parent-link loads before the tile loop and
   // keeps them live, and spills them, across it)
@@ -818,6 +869,16 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
       __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(stage + r * kRowPitch + col * 16),
                                   reinterpret_cast<u32x4*>(gbase + r * (kD * 2) + col * 16));
   }
+}
+
+template <int HD, bool kPaged, int kKG>
+__device__ __forceinline__ void run_share(bool tree, const MfmaArgs& a, Smem& sm, int b, int g, int row0,
+                                          int valid_rows, int key_begin, int n_pre, int P, int n,
+                                          bool final_out, int slot) {
+  if (tree)
+    attend<true, HD, kPaged, kKG>(a, sm, b, g, row0, valid_rows, key_begin, n_pre, P, n, final_out, slot);
+  else
+    attend<false, HD, kPaged, kKG>(a, sm, b, g, row0, valid_rows, key_begin, n_pre, P, n, final_out, slot);
 }
 
 // ---- the call's work axis (stream_plan.hpp), computed by each wave on its
@@ -871,7 +932,7 @@ __device__ __forceinline__ int64_t wave_scan_i64(int64_t x) {
   return dpp_add_i64<0x143, 0xC>(x);  // row_bcast:31 -> rows 2, 3
 }
 
-__device__ Axis axis_load(const MfmaArgs& a) {
+__device__ __forceinline__ Axis axis_load(const MfmaArgs& a) {
   const int lane = __lane_id();
   Axis ax{};
   if (a.B == 1) {
@@ -913,7 +974,7 @@ __device__ Axis axis_load(const MfmaArgs& a) {
 }
 
 // The sequence whose units hold axis position p (0 <= p < C).
-__device__ plan::SeqAt axis_find(const MfmaArgs& a, const Axis& ax, int64_t p) {
+__device__ __forceinline__ plan::SeqAt axis_find(const MfmaArgs& a, const Axis& ax, int64_t p) {
   plan::SeqAt r{};
   const uint64_t hit = __ballot(ax.len > 0 && ax.start <= p && p < ax.start + ax.len);
   if (hit != 0) {
@@ -982,7 +1043,7 @@ __device__ __forceinline__ int stream_index(int w, int W) { return (w % 8) * (W 
 // share one XCD (its L2 holds their common Q rows and K/V).  A unit with one
 // split writes its output directly; otherwise split sp leaves its partial in
 // slot (bg * max_splits + sp) * row_tiles + row tile.
-template <int HD, bool kPaged>
+template <int HD, bool kPaged, int kKG>
 __global__ void __launch_bounds__(kThreads, 1) attn_split_kernel(MfmaArgs a) {
   __shared__ __attribute__((aligned(16))) Smem sm;
   const int bg = blockIdx.x;
@@ -996,17 +1057,15 @@ __global__ void __launch_bounds__(kThreads, 1) attn_split_kernel(MfmaArgs a) {
   const int nsp = n_splits_of(P, n, a.split_keys, a.tree_alone);
   if (split >= nsp) return;
   const int valid_rows = a.G * n;
-  const int row0 = rtile * kTileRows;
+  const int row0 = rtile * a.tile_rows;
   if (row0 >= valid_rows) return;
   // Prefix keys [key_begin, key_begin + n_pre); a tree split of its own
   // starts at P with none.
   const int key_begin = min(split * a.split_keys, P);
   const int n_pre = min(a.split_keys, P - key_begin);
   const int slot = (bg * a.max_splits + split) * a.row_tiles + rtile;
-  if (split == nsp - 1)
-    attend<true, HD, kPaged>(a, sm, b, g, row0, valid_rows, key_begin, n_pre, P, n, nsp == 1, slot);
-  else
-    attend<false, HD, kPaged>(a, sm, b, g, row0, valid_rows, key_begin, n_pre, P, n, nsp == 1, slot);
+  run_share<HD, kPaged, kKG>(split == nsp - 1, a, sm, b, g, row0, valid_rows, key_begin, n_pre, P, n,
+                             nsp == 1, slot);
 }
 
 // Split plan merge, one wave per stacked row: combine the splits' partials
@@ -1033,7 +1092,7 @@ __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
   const int row = blockIdx.y * 4 + wv;
   const int lane = threadIdx.x % kWave;
   const int grp = lane >> 4, col = lane & 15;  // split offset, 8-dim chunk
-  const int Mpad = a.row_tiles * kTileRows;  // rows of a (sequence, kv head) unit set
+  const int Mpad = a.row_tiles * a.tile_rows;  // rows of a (sequence, kv head) unit set
   const int64_t part0 = static_cast<int64_t>(bg) * a.max_splits * Mpad + row;
   const unsigned char* op = reinterpret_cast<const unsigned char*>(a.ws_o + part0 * kD) + col * 16;
   const int64_t stride = static_cast<int64_t>(Mpad) * kD * 2;  // bytes between splits
@@ -1133,7 +1192,7 @@ __global__ void __launch_bounds__(256) attn_split_merge_few_kernel(MfmaArgs a) {
   if (halted(a.status)) return;
   const int row = blockIdx.y * 16 + threadIdx.x / 16;  // below row_tiles * kTileRows
   const int col = threadIdx.x % 16;
-  const int Mpad = a.row_tiles * kTileRows;
+  const int Mpad = a.row_tiles * a.tile_rows;
   const int64_t part0 = static_cast<int64_t>(bg) * a.max_splits * Mpad + row;
   f32x2 ml[kFewSplits];
   u32x4 o[kFewSplits];
@@ -1186,7 +1245,7 @@ __global__ void __launch_bounds__(256) attn_split_merge_few_kernel(MfmaArgs a) {
 // into LDS, then run one by one by the whole workgroup: the partition's state
 // (the sequence table, positions) is dead while the tile loop runs, which
 // keeps it out of the loop's registers.
-template <int HD, bool kPaged>
+template <int HD, bool kPaged, int kKG>
 __global__ void __launch_bounds__(kThreads, 1) attn_stream_kernel(MfmaArgs a) {
   __shared__ __attribute__((aligned(16))) Smem sm;
   if (halted(a.status)) return;
@@ -1244,12 +1303,8 @@ __global__ void __launch_bounds__(kThreads, 1) attn_stream_kernel(MfmaArgs a) {
       started = true;
       const ShareDesc d = sm.share[i];
       const int row0 = d.rt * kTileRows;
-      if (d.tree)
-        attend<true, HD, kPaged>(a, sm, d.b, d.g, row0, a.G * d.n, d.key_begin, d.n_pre, d.P, d.n,
-                     d.whole != 0, d.slot);
-      else
-        attend<false, HD, kPaged>(a, sm, d.b, d.g, row0, a.G * d.n, d.key_begin, d.n_pre, d.P, d.n,
-                      d.whole != 0, d.slot);
+      run_share<HD, kPaged, kKG>(d.tree != 0, a, sm, d.b, d.g, row0, a.G * d.n, d.key_begin, d.n_pre, d.P,
+                                 d.n, d.whole != 0, d.slot);
     }
     if (next_pos < 0) break;
     __syncthreads();  // every wave has read this round's shares
@@ -1439,7 +1494,16 @@ int64_t worst_split_key_cap(const AttnShape& s) {
   return split_key_cap(w);
 }
 
-static double plan_cost(int64_t P, int n, int64_t sk, bool alone, int64_t units, int64_t target) {
+// Two key groups when every unit of the call fits half of the waves.  (Mixed
+// calls stay with one: a choice per unit, with both loops in one kernel,
+// overran the instruction cache and lost 2-4% on batches of 32- to 220-row
+// units, where it gained 5-8% with all units of at most 128 rows.)
+bool two_key_groups(const AttnShape& s) { return s.Hq / s.Hkv * s.Nmax <= kTileRows / 2; }
+
+// Estimated time of a split plan, in key tiles of a 256-row unit (about 2 us).
+// `tile` is the cost of one key tile for the plan's units: a unit of at most
+// 128 rows works on each tile with two key groups.
+static double plan_cost(int64_t P, int n, int64_t sk, bool alone, int64_t units, int64_t target, double tile) {
   constexpr double kFixedTiles = 3.0, kMaskTiles = 0.5, kMergeTiles = 2.5;
   const int64_t tps = sk / kKT;
   const int64_t tree_tiles = (n + kKT - 1) / kKT;
@@ -1447,28 +1511,37 @@ static double plan_cost(int64_t P, int n, int64_t sk, bool alone, int64_t units,
   const int S = n_splits_of(static_cast<int>(P), n, static_cast<int>(sk), alone);
   double longest;
   if (pre <= 1) {
-    longest = static_cast<double>((P + kKT - 1) / kKT + tree_tiles) + kMaskTiles;
+    longest = tile * static_cast<double>((P + kKT - 1) / kKT + tree_tiles) + kMaskTiles;
   } else {
     const int64_t last = (P - (pre - 1) * sk + kKT - 1) / kKT;
     const double tree_split =
-        static_cast<double>(S > pre ? tree_tiles : last + tree_tiles) + kMaskTiles;
-    longest = std::max(static_cast<double>(tps), tree_split);
+        tile * static_cast<double>(S > pre ? tree_tiles : last + tree_tiles) + kMaskTiles;
+    longest = std::max(tile * static_cast<double>(tps), tree_split);
   }
   const int64_t rounds = (units * S + target - 1) / target;
   return static_cast<double>(rounds) * (longest + kFixedTiles) +
          (S > 1 ? kMergeTiles + S / 32.0 : 0.0);
 }
 
+constexpr double kHalfTile = 0.55;  // a key tile's cost for a unit of at most 128 rows
+
 void plan_split(const AttnShape& s, int num_cus, AttnPlan* p) {
   const int G = s.Hq / s.Hkv;
   const int rows = G * s.Nmax;
-  p->row_tiles = (rows + kTileRows - 1) / kTileRows;
   // A (sequence, kv head, row tile) unit is split along the keys into about
   // as many workgroups as keep one resident round of one workgroup per
   // compute unit busy (a second, nearly empty round would double the kernel
   // time).  That gives the shortest split considered; a split holds at least
   // two key tiles, at most the paged table's cap, and the merge kernel's
-  // table bounds the number of splits.
+  // table bounds the number of splits.  From there up to the cap, the split
+  // length (and whether the tree takes a split of its own) with the lowest
+  // estimated time: this balances the split that carries the tree against
+  // the others.  (Half-size units for longer trees too, to leave fewer compute
+  // units idle, were slower: 240 rows over a prefix of 2048 on 8 kv heads
+  // 14.1 us in 144 workgroups instead of 13.5 in 136.)
+  p->tile_rows = two_key_groups(s) ? kTileRows / 2 : kTileRows;
+  p->row_tiles = (rows + p->tile_rows - 1) / p->tile_rows;
+  const double tile = two_key_groups(s) ? kHalfTile : 1.0;
   const int64_t units = static_cast<int64_t>(s.B) * s.Hkv * p->row_tiles;
   const int64_t target = num_cus;
   const int64_t want = std::max<int64_t>(1, target / units);
@@ -1478,18 +1551,15 @@ void plan_split(const AttnShape& s, int num_cus, AttnPlan* p) {
   sk0 = std::max<int64_t>(sk0, (mp + kMaxMergeSplits - 1) / kMaxMergeSplits);
   sk0 = std::max<int64_t>((sk0 + kKT - 1) / kKT * kKT, 2 * kKT);
   sk0 = std::min(sk0, cap);
-  // From there up to the cap, the split length (and whether the tree takes a
-  // split of its own) with the lowest estimated time: this balances the
-  // split that carries the tree against the others.
   int64_t best_sk = sk0;
   bool best_alone = false;
-  double best = plan_cost(mp, s.Nmax, sk0, false, units, target);
+  double best = plan_cost(mp, s.Nmax, sk0, false, units, target, tile);
   for (int64_t sk = sk0; sk <= cap; sk += kKT) {
     for (int alone = 0; alone < 2; ++alone) {
       if (alone && n_splits_of(static_cast<int>(mp), s.Nmax, static_cast<int>(sk), 1) >
                        kMaxMergeSplits)
         continue;
-      const double c = plan_cost(mp, s.Nmax, sk, alone != 0, units, target);
+      const double c = plan_cost(mp, s.Nmax, sk, alone != 0, units, target, tile);
       if (c < best) {
         best = c;
         best_sk = sk;
@@ -1506,8 +1576,7 @@ void plan_split(const AttnShape& s, int num_cus, AttnPlan* p) {
   // None when no sequence can have more than one split.
   const int64_t pre0 = (mp + sk0 - 1) / sk0;
   const int64_t bound = pre0 <= 1 ? 1 : std::min<int64_t>(pre0 + 1, kMaxMergeSplits);
-  const int64_t Mpad = static_cast<int64_t>(p->row_tiles) * kTileRows;
-  const int64_t slots = static_cast<int64_t>(s.B) * s.Hkv * bound * Mpad;
+  const int64_t slots = units * bound * p->tile_rows;
   p->workspace_bytes =
       bound > 1 ? static_cast<size_t>(slots) * (kD * sizeof(uint16_t) + 2 * sizeof(float)) : 0;
   p->mfma = true;
@@ -1540,6 +1609,21 @@ void plan_mfma(const AttnShape& s, int num_cus, AttnPlan* p) {
     plan_stream(s, num_cus, p);
   else
     plan_split(s, num_cus, p);
+}
+
+// launch(head size, paged, key groups), as compile-time constants.
+template <class Launch>
+void pick_kernel(const AttnShape& s, bool paged, Launch launch) {
+  const auto with_groups = [&](auto d, auto pg) {
+    if (two_key_groups(s)) launch(d, pg, std::integral_constant<int, 2>{});
+    else launch(d, pg, std::integral_constant<int, 1>{});
+  };
+  const auto with_layout = [&](auto d) {
+    if (paged) with_groups(d, std::true_type{});
+    else with_groups(d, std::false_type{});
+  };
+  if (s.d == 64) with_layout(std::integral_constant<int, 64>{});
+  else with_layout(std::integral_constant<int, 128>{});
 }
 
 hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q,
@@ -1579,23 +1663,18 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
     a.max_splits = p.max_splits;
     a.tree_alone = p.tree_alone ? 1 : 0;
     a.row_tiles = p.row_tiles;
-    const size_t slots = static_cast<size_t>(s.B) * s.Hkv * p.max_splits * p.row_tiles * kTileRows;
+    a.tile_rows = p.tile_rows;
+    const size_t slots = static_cast<size_t>(s.B) * s.Hkv * p.max_splits * p.row_tiles * p.tile_rows;
     a.ws_ml = reinterpret_cast<float*>(ws + slots * kD * 2);
     const dim3 grid(s.B * s.Hkv, p.row_tiles, p.max_splits);
-    const bool paged = a.block_table != nullptr;
-    if (s.d == 64 && paged)
-      hipLaunchKernelGGL((attn_split_kernel<64, true>), grid, dim3(kThreads), 0, stream, a);
-    else if (s.d == 64)
-      hipLaunchKernelGGL((attn_split_kernel<64, false>), grid, dim3(kThreads), 0, stream, a);
-    else if (paged)
-      hipLaunchKernelGGL((attn_split_kernel<128, true>), grid, dim3(kThreads), 0, stream, a);
-    else
-      hipLaunchKernelGGL((attn_split_kernel<128, false>), grid, dim3(kThreads), 0, stream, a);
+    pick_kernel(s, a.block_table != nullptr, [&](auto d, auto paged, auto kg) {
+      hipLaunchKernelGGL((attn_split_kernel<d(), paged(), kg()>), grid, dim3(kThreads), 0, stream, a);
+    });
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.max_splits == 1) return e;  // one split: the output is final
     // (sequence, kv head) fastest, as for the attention grid: a head's merge
     // runs on the XCD whose workgroups wrote its partials.
-    const unsigned mrows = static_cast<unsigned>(p.row_tiles * kTileRows);
+    const unsigned mrows = static_cast<unsigned>(p.row_tiles * p.tile_rows);
     if (p.max_splits <= kFewSplits) {
       const dim3 fgrid(s.B * s.Hkv, mrows / 16);
       if (s.d == 64)
@@ -1615,16 +1694,11 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
   a.ws_ml = reinterpret_cast<float*>(ws + slots * kD * 2);
   a.ws_desc = reinterpret_cast<MergeDesc*>(ws + slots * (kD * 2 + 2 * sizeof(float)));
   a.W = p.grid;
+  a.tile_rows = kTileRows;
   a.max_units = static_cast<int>(max_units(s));
-  const bool paged = a.block_table != nullptr;
-  if (s.d == 64 && paged)
-    hipLaunchKernelGGL((attn_stream_kernel<64, true>), dim3(p.grid), dim3(kThreads), 0, stream, a);
-  else if (s.d == 64)
-    hipLaunchKernelGGL((attn_stream_kernel<64, false>), dim3(p.grid), dim3(kThreads), 0, stream, a);
-  else if (paged)
-    hipLaunchKernelGGL((attn_stream_kernel<128, true>), dim3(p.grid), dim3(kThreads), 0, stream, a);
-  else
-    hipLaunchKernelGGL((attn_stream_kernel<128, false>), dim3(p.grid), dim3(kThreads), 0, stream, a);
+  pick_kernel(s, a.block_table != nullptr, [&](auto d, auto paged, auto kg) {
+    hipLaunchKernelGGL((attn_stream_kernel<d(), paged(), kg()>), dim3(p.grid), dim3(kThreads), 0, stream, a);
+  });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // One merge workgroup column per possible unit, 4 * kMergeRows rows per workgroup.

@@ -13,12 +13,13 @@ pytestmark = pytest.mark.gpu
 
 
 def _prefix_with_splits(splits, N, Hq, Hkv, d):
-    """The shortest prefix that one sequence's plan cuts into `splits` pieces."""
+    """The shortest prefix that one sequence's plan cuts into `splits` pieces or
+    more (the plan skips some counts)."""
     def grid(P):
         return ltd.attn_grid(1, N, Hq, Hkv, d, P, ltd.DTYPE_BF16, P + N)
     units = grid(1)
     for P in range(65, 12000, 16):
-        if grid(P) == units * splits:
+        if grid(P) >= units * splits:
             return P
     pytest.fail(f"no prefix gives {splits} splits")
 
@@ -26,7 +27,7 @@ def _prefix_with_splits(splits, N, Hq, Hkv, d):
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("splits", [3, 8, 9, 32, 33, 64, 65])
 def test_split_counts(splits, d):
-    Hq, Hkv, N = 8, 2, 33
+    Hq, Hkv, N = 8, 2, 31  # 124 rows: one row tile
     P = _prefix_with_splits(splits, N, Hq, Hkv, d)
     rng = np.random.default_rng(splits * 2 + d)
     tree = W.tree_uniform_parent(rng, N)
