@@ -50,6 +50,8 @@
 //                        the search.
 // Element arithmetic is float32, every sum over the vocabulary is finished in
 // double.
+#include <type_traits>
+
 #include "ltd_device.hpp"
 #include "ltd_launch.hpp"
 
@@ -101,6 +103,26 @@ __device__ __forceinline__ int link(const int32_t* __restrict__ parents, int64_t
   return j == 0 ? -1 : min(max(parents[nb + j], 0), j - 1);
 }
 
+// Node i's children among nodes 0 .. n - 1 as bits of 64-node words, found by
+// one wave (every wave of a workgroup finds them for itself: no LDS, no
+// barrier).  All Nmax links are loaded, before n is known and apart from their
+// use, so that other loads can be requested in between.
+constexpr int kNodeWords = LTD_MAX_NODES / kWave;
+struct Links {
+  int p[kNodeWords];  // lane l, word k: node l + 64 k
+};
+__device__ __forceinline__ Links load_links(const int32_t* __restrict__ parents, int64_t nb,
+                                            int Nmax, int lane) {
+  Links r;
+#pragma unroll
+  for (int k = 0; k < kNodeWords; ++k) r.p[k] = parents[nb + min(k * kWave + lane, Nmax - 1)];
+  return r;
+}
+__device__ __forceinline__ uint64_t kids_word(const Links& ln, int k, int n, int i, int lane) {
+  const int j = k * kWave + lane;
+  return __ballot(j < n && j > i && min(max(ln.p[k], 0), j - 1) == i);
+}
+
 struct NodeStats {  // per (sequence, node, chunk)
   float m;   // max of logits / T over the chunk
   float z;   // sum of exp(logits / T - m)
@@ -132,11 +154,11 @@ __global__ void __launch_bounds__(kStatThreads) sample_stats_kernel(
     const int32_t* __restrict__ parents, const int32_t* __restrict__ n_nodes, int Nmax, int Voc,
     float inv_t, NodeStats* __restrict__ ws, const int32_t* status) {
   __shared__ float red_s[3][kStatThreads / kWave];
-  __shared__ int has_child_s;
   if (halted(status)) return;
   const int chunk = blockIdx.x, i = blockIdx.y, b = blockIdx.z;
   const int chunks = gridDim.x;
   const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+  const Links ln = load_links(parents, static_cast<int64_t>(b) * Nmax, Nmax, lane);
   const int n = min(max(n_nodes[b], 1), Nmax);
   if (i >= n) return;  // uniform for the block
   const int64_t row = (static_cast<int64_t>(b) * Nmax + i) * Voc;
@@ -148,13 +170,10 @@ __global__ void __launch_bounds__(kStatThreads) sample_stats_kernel(
     const float lv = logits[row + min(v, Voc - 1)];
     l[k] = v < Voc ? lv * inv_t : -INFINITY;
   }
-  // the draft row is read only for nodes with children
-  if (t == 0) has_child_s = 0;
-  __syncthreads();
-  for (int j = t; j < n; j += kStatThreads)
-    if (j > i && link(parents, static_cast<int64_t>(b) * Nmax, j) == i) has_child_s = 1;
-  __syncthreads();
-  const bool want_q = has_child_s != 0;
+  uint64_t any = 0;  // the draft row is read only for nodes with children
+#pragma unroll
+  for (int k = 0; k < kNodeWords; ++k) any |= kids_word(ln, k, n, i, lane);
+  const bool want_q = any != 0;
 #pragma unroll
   for (int k = 0; k < kPerThread; ++k) {
     const int v = base + k * kStatThreads + t;
@@ -286,7 +305,7 @@ struct NodeTotals {
   float Mf;
   double Z, QS;
 };
-__device__ NodeTotals merge_node_stats_of(const NodeStats st, int chunks, int lane) {
+__device__ NodeTotals merge_node_stats(const NodeStats st, int chunks, int lane) {
   const float m_l = lane < chunks ? st.m : -INFINITY;
   float Mf = m_l;
   Mf = fmaxf(Mf, lane_xor_f<32>(Mf, lane));
@@ -315,9 +334,6 @@ __device__ NodeTotals merge_node_stats_of(const NodeStats st, int chunks, int la
     ql += __longlong_as_double(static_cast<long long>(oq));
   }
   return NodeTotals{Mf, zl, ql};
-}
-__device__ NodeTotals merge_node_stats(const NodeStats* __restrict__ st_row, int chunks, int lane) {
-  return merge_node_stats_of(st_row[min(lane, chunks - 1)], chunks, lane);
 }
 
 constexpr double kLog2e = 1.4426950408889634;
@@ -388,81 +404,70 @@ __device__ double wave_range_sum(const float* __restrict__ l, const float* __res
   return wave_sum_d(acc, lane);
 }
 
-// Per (node with at least `level` children, chunk): the residual mass
-// sum_v max(P(v) - g Q(v), 0) over the chunk after the node's level-th
+// Per (node with at least kLevel children, chunk): the residual mass
+// sum_v max(P(v) - g Q(v), 0) over the chunk after the node's kLevel-th
 // rejection, with the walk's own parameters and element arithmetic.  Level 1
 // is at g = 1; level k replays the node's first k - 1 rejections from the
 // totals of levels 1 .. k - 1 (tables `mass` + (l - 1) * level_stride), the
 // way the walk advances its state.  Other nodes' entries read as 0.
+// The kernel is a chain of dependent loads, so each is requested as soon as its
+// address is known: links, tokens, the chunk partials and the earlier levels'
+// entries at once; the rows once the wave has counted the node's children
+// itself, before wave 0 merges the partials and replays the rejections (60 nodes,
+// 20 with children, 128256 tokens: 7.5, 6.0 and 5.9 us for levels 1 to 3 with the
+// children gathered through LDS between barriers and the partials merged first,
+// 6.7, 5.7 and 5.7 now; sample_stats_kernel 8.6 -> 8.1; a call 77.7 -> 76.0).
+template <int kLevel>
 __global__ void __launch_bounds__(kStatThreads) sample_mass_kernel(
     const float* __restrict__ logits, const float* __restrict__ draft_probs,
     const int32_t* __restrict__ draft_tokens, const int32_t* __restrict__ parents,
     const int32_t* __restrict__ n_nodes, int Nmax, int Voc, float inv_t,
-    const NodeStats* __restrict__ ws, MassEntry* __restrict__ mass, int level,
-    int64_t level_stride, const int32_t* status) {
-  static_assert(kStatThreads >= LTD_MAX_NODES, "one thread per node for the child bits");
-  __shared__ NodeTotals nt_s;
-  __shared__ uint64_t kids_s[kStatThreads / kWave];
-  __shared__ int tok_s[kLevels];
-  __shared__ int ctok_s[LTD_MAX_NODES];  // tokens of the node's children
-  __shared__ double g_s;
+    const NodeStats* __restrict__ ws, MassEntry* __restrict__ mass, int64_t level_stride,
+    const int32_t* status) {
+  static_assert(kLevel >= 1 && kLevel <= kLevels, "");
+  __shared__ Residual res_s;
   __shared__ double red_s[kStatThreads / kWave];
   __shared__ double keep_s[kStatThreads / kWave];
   if (halted(status)) return;
   const int chunk = blockIdx.x, i = blockIdx.y, b = blockIdx.z;
   const int chunks = gridDim.x;
   const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
-  const int n = min(max(n_nodes[b], 1), Nmax);
-  if (i >= n) return;  // uniform for the block
   const int64_t nb = static_cast<int64_t>(b) * Nmax;
   const int64_t row = (nb + i) * Voc;
-  MassEntry* out = mass + (level - 1) * level_stride + (nb + i) * chunks + chunk;
-  {  // the node's children as bits, thread j for node j, and their tokens
-    const bool kid = t < n && t > i && link(parents, nb, t) == i;
-    const int tok = min(max(draft_tokens[nb + min(t, n - 1)], 0), Voc - 1);
-    const uint64_t bits = __ballot(kid);
-    if (lane == 0) kids_s[w] = bits;
-    if (kid) ctok_s[t] = tok;
-  }
-  if (w == 0) {
-    const NodeTotals nt = merge_node_stats(ws + (nb + i) * chunks, chunks, lane);
-    if (lane == 0) nt_s = nt;
-  }
-  __syncthreads();
-  int n_kids = 0;
+  MassEntry* out = mass + (kLevel - 1) * level_stride + (nb + i) * chunks + chunk;
+  const Links ln = load_links(parents, nb, Nmax, lane);
+  int tok[kNodeWords];
 #pragma unroll
-  for (int word = 0; word < kStatThreads / kWave; ++word) n_kids += __popcll(kids_s[word]);
-  if (n_kids < level) {  // uniform: the node never rejects `level` times
+  for (int k = 0; k < kNodeWords; ++k) tok[k] = draft_tokens[nb + min(k * kWave + lane, Nmax - 1)];
+  const int cl = min(lane, chunks - 1);
+  NodeStats st_c{};
+  MassEntry prev[kLevel];  // (the last one unused)
+  if (w == 0) {
+    st_c = ws[(nb + i) * chunks + cl];
+#pragma unroll
+    for (int k = 0; k < kLevel - 1; ++k) prev[k] = mass[k * level_stride + (nb + i) * chunks + cl];
+  }
+  const int n = min(max(n_nodes[b], 1), Nmax);
+  if (i >= n) return;  // uniform for the block
+  // the node's first kLevel children's tokens, in ascending order
+  int n_kids = 0;
+  int ex[kLevel];
+#pragma unroll
+  for (int j = 0; j < kLevel; ++j) ex[j] = -1;
+#pragma unroll
+  for (int k = 0; k < kNodeWords; ++k) {
+    uint64_t bits = kids_word(ln, k, n, i, lane);
+    while (bits != 0 && n_kids < kLevel) {
+      const int x = __builtin_amdgcn_readlane(tok[k], __ffsll(static_cast<long long>(bits)) - 1);
+      bits &= bits - 1;
+#pragma unroll
+      for (int j = 0; j < kLevel; ++j) ex[j] = j == n_kids ? min(max(x, 0), Voc - 1) : ex[j];
+      ++n_kids;
+    }
+  }
+  if (n_kids < kLevel) {  // uniform for the block: the node never rejects kLevel times
     if (t == 0) *out = MassEntry{0.0, 0.0};
     return;
-  }
-  if (t == 0) {  // its first `level` children's tokens, in ascending order
-    int nk = 0;
-    for (int word = 0; word < kStatThreads / kWave && nk < level; ++word) {
-      uint64_t bits = kids_s[word];
-      while (bits != 0 && nk < level) {
-        const int c = word * kWave + __ffsll(static_cast<long long>(bits)) - 1;
-        bits &= bits - 1;
-        tok_s[nk++] = ctok_s[c];
-      }
-    }
-  }
-  __syncthreads();
-  const NodeTotals nt = nt_s;
-  // wave 0's loads for the replay first, then every thread's share of the
-  // chunk's rows, in flight while the residual's g is worked out
-  double prev_mass[kLevels - 1], prev_keep[kLevels - 1];
-  if (w == 0) {
-#pragma unroll
-    for (int k = 0; k < kLevels - 1; ++k) {
-      prev_mass[k] = 0.0;
-      prev_keep[k] = 0.0;
-      if (k < level - 1 && lane < chunks) {
-        const MassEntry e = mass[k * level_stride + (nb + i) * chunks + lane];
-        prev_mass[k] = e.mass;
-        prev_keep[k] = e.keep;
-      }
-    }
   }
   const int base = chunk * kChunk;
   float l[kPerThread], q[kPerThread];
@@ -472,27 +477,24 @@ __global__ void __launch_bounds__(kStatThreads) sample_mass_kernel(
     l[k] = logits[v];
     q[k] = draft_probs[v];
   }
-  if (w == 0) {  // g after `level` rejections: the walk's state, replayed
+  if (w == 0) {  // g after kLevel rejections: the walk's state, replayed
+    const NodeTotals nt = merge_node_stats(st_c, chunks, lane);
     RejState st{0.0, 1.0, 1.0};
 #pragma unroll
-    for (int k = 0; k < kLevels - 1; ++k) {
-      if (k < level - 1) {
-        const double tot = wave_sum_d(prev_mass[k], lane);
-        const double keep = wave_sum_d(prev_keep[k], lane);
-        const double g2 = next_g(st);
-        reject(st, g2, tot, left_mass(keep, nt.QS));
-      }
+    for (int k = 0; k < kLevel - 1; ++k) {
+      const double tot = wave_sum_d(lane < chunks ? prev[k].mass : 0.0, lane);
+      const double keep = wave_sum_d(lane < chunks ? prev[k].keep : 0.0, lane);
+      const double g2 = next_g(st);
+      reject(st, g2, tot, left_mass(keep, nt.QS));
     }
-    if (lane == 0) g_s = next_g(st);
+    const Residual r0 = residual_params(nt, inv_t, next_g(st));
+    if (lane == 0) res_s = r0;
   }
   __syncthreads();
-  const Residual r = residual_params(nt, inv_t, g_s);
-  // The draft sum outside the first `level` children's tokens: a sum of
+  const Residual r = res_s;
+  // The draft sum outside the first kLevel children's tokens: a sum of
   // non-negative terms, so float partials keep it to a relative error, however
   // small it is (the difference it replaces would lose every digit).
-  int ex[kLevels];
-#pragma unroll
-  for (int j = 0; j < kLevels; ++j) ex[j] = j < level ? tok_s[j] : -1;
   double d = 0.0;
   float kf = 0.f;
 #pragma unroll
@@ -502,7 +504,7 @@ __global__ void __launch_bounds__(kStatThreads) sample_mass_kernel(
       d += static_cast<double>(residual_elem(l[k], q[k], r));
       bool gone = false;
 #pragma unroll
-      for (int j = 0; j < kLevels; ++j) gone = gone || ex[j] == v;
+      for (int j = 0; j < kLevel; ++j) gone = gone || ex[j] == v;
       kf += gone ? 0.f : q[k];
     }
   }
@@ -558,7 +560,7 @@ __device__ __forceinline__ NodeLoads node_loads(const NodeStats* __restrict__ ws
 __device__ void node_merge(const NodeLoads& ld, const int32_t* par_s, int n, int v, int chunks,
                            int lane, double* node_out, double (*mass_out)[kLevels + 1]) {
   const NodeStats st = ld.st;
-  const NodeTotals nt = merge_node_stats_of(st, chunks, lane);
+  const NodeTotals nt = merge_node_stats(st, chunks, lane);
   const bool kids = child_any(par_s, n, v, lane);
   const double m0c =
       st.m != -INFINITY ? static_cast<double>(st.z * __expf(st.m - nt.Mf)) / nt.Z : 0.0;
@@ -938,10 +940,15 @@ hipError_t launch_sampling(const float* logits, const float* draft_probs,
   hipLaunchKernelGGL(sample_stats_kernel, dim3(chunks, Nmax, B), dim3(kStatThreads), 0, stream,
                      logits, draft_probs, parents, n_nodes, Nmax, Voc, inv_t, ws, status);
   // level k needs the totals of level k - 1: one launch per level
-  for (int level = 1; level <= kLevels; ++level)
-    hipLaunchKernelGGL(sample_mass_kernel, dim3(chunks, Nmax, B), dim3(kStatThreads), 0, stream,
-                       logits, draft_probs, draft_tokens, parents, n_nodes, Nmax, Voc, inv_t, ws,
-                       mass, level, level_stride, status);
+  const auto launch_mass = [&](auto level) {
+    hipLaunchKernelGGL(sample_mass_kernel<level()>, dim3(chunks, Nmax, B), dim3(kStatThreads), 0,
+                       stream, logits, draft_probs, draft_tokens, parents, n_nodes, Nmax, Voc, inv_t,
+                       ws, mass, level_stride, status);
+  };
+  static_assert(kLevels == 3, "one launch per level");
+  launch_mass(std::integral_constant<int, 1>{});
+  launch_mass(std::integral_constant<int, 2>{});
+  launch_mass(std::integral_constant<int, 3>{});
   hipLaunchKernelGGL(sample_walk_kernel, dim3(B), dim3(kWalkThreads), 0, stream, logits,
                      draft_probs, draft_tokens, parents, n_nodes, uniforms, Nmax, Voc, inv_t, ws,
                      mass, level_stride, chunks, accepted_nodes, out_tokens, n_accepted, status);
