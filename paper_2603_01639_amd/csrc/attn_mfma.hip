@@ -1342,7 +1342,10 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   for (int i = 0; i < kRowSteps; ++i) r[i] = min(r0 + 4 * i + (lane >> 4), rows - 1);
   const int npieces = d.pieces;
   // Slot of piece k: its place alone when every range holds an item of the
-  // unit (always, but for calls with fewer items than workgroups).
+  // unit, else (calls with fewer items than workgroups, as when Nmax is far
+  // above the trees' sizes) looked up in the partition.  A lookup is long, so
+  // the lanes take 64 pieces' at once (one by one: sequences of 2 and 4 nodes
+  // over prefixes of 711, one kv head, Nmax 256, 38.5 us a call; now 23.3).
   auto slot_of = [&](int k) -> int {
     if (k >= npieces) return -1;
     if (d.dense) return plan::dense_piece_slot(d.sa, k);
@@ -1360,12 +1363,14 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
     wsum[i] = 0.f;
     M[i] = -INFINITY;
   }
+  int my_slot = -1;  // of piece k0 - k0 % 64 + lane
   for (int k0 = 0; k0 < npieces; k0 += kBatch) {
+    if (k0 % kWave == 0) my_slot = slot_of(k0 + lane);
     f32x2 ml[kRowSteps][kBatch];
     u32x4 o[kRowSteps][kBatch];
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
-      const int slot = slot_of(k0 + j);
+      const int slot = __builtin_amdgcn_readlane(my_slot, (k0 + j) % kWave);
 #pragma unroll
       for (int i = 0; i < kRowSteps; ++i) {
         ml[i][j] = (f32x2){-INFINITY, 0.f};
