@@ -117,6 +117,7 @@ struct MfmaArgs {
   // the tree may take a split of its own, row tiles per (sequence, kv head)
   int split_keys, max_splits, tree_alone, row_tiles;
   int tile_rows;  // stacked rows per unit
+  int merge_early;  // split plan: the merge requests partials before it knows the sequence's lengths
   float scale_log2;
   float lazy_gap;  // kLazyMax / scale_log2: the raw-score margin of the lazy max
 };
@@ -1068,16 +1069,27 @@ __global__ void __launch_bounds__(kThreads, 1) attn_split_kernel(MfmaArgs a) {
                              nsp == 1, slot);
 }
 
+// Splits whose partials a merge combines for a stacked row: 0 for a row past
+// the tree, 1 when the attention kernel wrote the row's output.  (Clamped so
+// that a prefix above the planned maximum cannot index past the workspace;
+// such input is malformed and caught when validation is on.)
+__device__ __forceinline__ int merge_splits(const MfmaArgs& a, int b, int row) {
+  const int n = a.n_nodes[b];
+  const int P = a.prefix_len[b];
+  if (row >= a.G * n) return 0;
+  return min(n_splits_of(P, n, a.split_keys, a.tree_alone), a.max_splits);
+}
+
 // Split plan merge, one wave per stacked row: combine the splits' partials
 //   out = sum_s w_s * Ohat_s / sum_s w_s,  w_s = 2^(m_s - M) * l_s,  M = max_s m_s,
 // where Ohat_s = O_s / l_s is the split's normalised output (bf16).  Lane s
 // takes split s's (m, l); the 4 groups of 16 lanes each read one split's row
 // (16 bytes = 8 dims per lane) per step, so 4 splits' rows are in flight per
-// load, and the groups' sums are added with two lane exchanges.  The kernel
-// is latency-bound, so the (m, l) pairs and the first 32 splits' rows are
-// requested before the sequence's prefix length and node count arrive: every
-// row of the grid is inside the workspace's Mpad rows, and every split index
-// below max_splits inside its splits.  (A second round for the splits past 16
+// load, and the groups' sums are added with two lane exchanges.  A small
+// launch is latency-bound, so the (m, l) pairs and the first 32 splits' rows are
+// then requested before the sequence's prefix length and node count arrive
+// (merge_early): every row of the grid is inside the workspace's Mpad rows, and
+// every split index below max_splits inside its splits.  (A second round for the splits past 16
 // and reductions through the LDS crossbar made it 5.0 us instead of 4.1 for
 // 240 rows of 17 splits on 8 kv heads.)
 template <int HD>
@@ -1096,22 +1108,22 @@ __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
   const int64_t part0 = static_cast<int64_t>(bg) * a.max_splits * Mpad + row;
   const unsigned char* op = reinterpret_cast<const unsigned char*>(a.ws_o + part0 * kD) + col * 16;
   const int64_t stride = static_cast<int64_t>(Mpad) * kD * 2;  // bytes between splits
+  int live = a.max_splits;  // splits whose partials are read
+  if (!a.merge_early) {
+    live = merge_splits(a, b, row);
+    if (live <= 1) return;
+  }
   f32x2 ml0 = {-INFINITY, 0.f};
-  if (lane < a.max_splits) ml0 = *reinterpret_cast<const f32x2*>(a.ws_ml + (part0 + lane * Mpad) * 2);
+  if (lane < live) ml0 = *reinterpret_cast<const f32x2*>(a.ws_ml + (part0 + lane * Mpad) * 2);
   u32x4 o0[kFirst / 4];
 #pragma unroll
   for (int u = 0; u < kFirst / 4; ++u) {
     const int sp = 4 * u + grp;
-    o0[u] = sp < a.max_splits ? *reinterpret_cast<const u32x4*>(op + sp * stride)
-                              : (u32x4){0u, 0u, 0u, 0u};
+    o0[u] = sp < live ? *reinterpret_cast<const u32x4*>(op + sp * stride)
+                      : (u32x4){0u, 0u, 0u, 0u};
   }
-  const int n = a.n_nodes[b];
-  const int P = a.prefix_len[b];
-  if (row >= a.G * n) return;
-  // (clamped so that a prefix above the planned maximum cannot index past the
-  // workspace; such input is malformed and caught when validation is on)
-  const int n_splits = min(n_splits_of(P, n, a.split_keys, a.tree_alone), a.max_splits);
-  if (n_splits == 1) return;  // the attention kernel wrote this row's output
+  const int n_splits = a.merge_early ? merge_splits(a, b, row) : live;
+  if (n_splits <= 1) return;
   float M = lane < n_splits ? ml0.x : -INFINITY;
   for (int s = lane + kWave; s < n_splits; s += kWave) M = fmaxf(M, a.ws_ml[(part0 + s * Mpad) * 2]);
   M = wave_max_dpp(M);
@@ -1184,6 +1196,15 @@ __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
 // of 4 splits on 8 kv heads take 5.7 us here and 9.7 us there.  From 9 splits
 // on the rows are few, and a wave per row keeps more loads in flight.
 constexpr int kFewSplits = 8;
+// The launch's partial rows, in bytes, up to which the merges request them
+// before they know which were written.  Small merges wait on one round of
+// loads less (13.47 -> 13.35 us for 32/8 heads, prefix 2048, 60 nodes: 9 MB); in
+// large ones other waves hide the wait, and where max_prefix or Nmax is far above
+// the call's lengths the rows are mostly traffic for nothing (4 sequences of
+// 64/8 heads, 14-42 nodes, prefixes 2225-5070 in 16-row blocks under
+// max_prefix 81120 and Nmax 256, 671 MB: 153 us, now 69.5).  At 17 MB (64/8 heads,
+// prefix 4096, 256 nodes) the two are alike.
+constexpr size_t kEarlyMergeBytes = size_t{16} << 20;
 template <int HD>
 __global__ void __launch_bounds__(256) attn_split_merge_few_kernel(MfmaArgs a) {
   const int bg = blockIdx.x;
@@ -1194,23 +1215,25 @@ __global__ void __launch_bounds__(256) attn_split_merge_few_kernel(MfmaArgs a) {
   const int col = threadIdx.x % 16;
   const int Mpad = a.row_tiles * a.tile_rows;
   const int64_t part0 = static_cast<int64_t>(bg) * a.max_splits * Mpad + row;
+  int live = a.max_splits;  // splits whose partials are read
+  if (!a.merge_early) {
+    live = merge_splits(a, b, row);
+    if (live <= 1) return;
+  }
   f32x2 ml[kFewSplits];
   u32x4 o[kFewSplits];
 #pragma unroll
   for (int s = 0; s < kFewSplits; ++s) {
     ml[s] = (f32x2){-INFINITY, 0.f};
     o[s] = (u32x4){0u, 0u, 0u, 0u};
-    if (s < a.max_splits) {
+    if (s < live) {
       const int64_t r = part0 + static_cast<int64_t>(s) * Mpad;
       ml[s] = *reinterpret_cast<const f32x2*>(a.ws_ml + r * 2);
       o[s] = *reinterpret_cast<const u32x4*>(a.ws_o + r * kD + col * 8);
     }
   }
-  const int n = a.n_nodes[b];
-  const int P = a.prefix_len[b];
-  if (row >= a.G * n) return;
-  const int n_splits = min(n_splits_of(P, n, a.split_keys, a.tree_alone), a.max_splits);
-  if (n_splits == 1) return;  // the attention kernel wrote this row's output
+  const int n_splits = a.merge_early ? merge_splits(a, b, row) : live;
+  if (n_splits <= 1) return;
   float M = -INFINITY;
 #pragma unroll
   for (int s = 0; s < kFewSplits; ++s)
@@ -1671,6 +1694,7 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
     a.tile_rows = p.tile_rows;
     const size_t slots = static_cast<size_t>(s.B) * s.Hkv * p.max_splits * p.row_tiles * p.tile_rows;
     a.ws_ml = reinterpret_cast<float*>(ws + slots * kD * 2);
+    a.merge_early = slots * kD * 2 <= kEarlyMergeBytes ? 1 : 0;
     const dim3 grid(s.B * s.Hkv, p.row_tiles, p.max_splits);
     pick_kernel(s, a.block_table != nullptr, [&](auto d, auto paged, auto kg) {
       hipLaunchKernelGGL((attn_split_kernel<d(), paged(), kg()>), grid, dim3(kThreads), 0, stream, a);

@@ -84,3 +84,30 @@ def test_time_of_sparse_pieces():
     t = _times(loose, tight)
     U.log(f"[loose bounds] Nmax 256: {t[0]:.1f} us, Nmax 4: {t[1]:.1f} us")
     assert t[0] < 2.5 * t[1], t  # 3.3 one by one, 2.0 by lanes
+
+
+# Plans of 6 splits (the merge for up to 8), 18 (a wave a row, every split
+# requested up front) and more than 32; and, with 256-node bounds on 8 kv
+# heads, plans of 4 and 20 whose partials are not requested before the lengths
+# are known.
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("Hq,Hkv,Nmax,max_prefix,lo,hi", [(8, 2, 31, 640, 2, 8), (8, 2, 31, 2200, 9, 32),
+                                                          (8, 2, 31, 6300, 33, 64), (64, 8, 256, 6000, 2, 8),
+                                                          (64, 8, 256, 40000, 9, 32)])
+def test_fewer_splits_than_planned(Hq, Hkv, Nmax, max_prefix, lo, hi, d):
+    """One sequence whose prefix gives 1, 2 or some of the splits that the plan
+    for max_prefix allows: partials that no workgroup wrote are not used."""
+    grid, units = (ltd.attn_grid(1, Nmax, Hq, Hkv, d, p, ltd.DTYPE_BF16, max_prefix + Nmax)
+                   for p in (max_prefix, 1))
+    assert lo <= grid // units <= hi
+    for P in (0, 1, 128, 129, max_prefix // 2):
+        _check(_batch(Hq, Hkv, d, [P], [13], Nmax), max_prefix)
+
+
+def test_time_of_a_loose_prefix_bound():
+    """A merge that requests every planned split's rows took this call from 101
+    to 153 us; with max_prefix tight it takes 41."""
+    b = _batch(64, 8, 128, [2225, 5070, 3000, 4000], [14, 42, 20, 30], 256, block=16)
+    t = _times(_call(b, 81120)[0], _call(b, 5070)[0])
+    U.log(f"[loose bounds] max_prefix 81120: {t[0]:.1f} us, 5070: {t[1]:.1f} us")
+    assert t[0] < 2.5 * t[1], t  # 3.7 with every planned split requested, 1.7 without
