@@ -1339,17 +1339,24 @@ __global__ void __launch_bounds__(kThreads, 1) attn_stream_kernel(MfmaArgs a) {
 // workgroup order, where Ohat_p = O_p / l_p is the piece's normalised output
 // (bf16).  blockIdx.x = the unit (its entry in the merge table says whether it
 // was cut), blockIdx.y picks 4 * kMergeRows of its rows: each wave takes
-// kMergeRows rows, 16 lanes (16 bytes of a row each) and kRowSteps rows per
-// lane, so a load reads whole rows.  The pieces come in batches of kBatch with
-// all their loads in flight, under a running max (each batch rescales the
-// sums at most once).  (With 4 lanes a row, 64 bytes
-// each, a load touched a quarter of every line: 16 sequences of 64/8 heads,
-// prefixes 1024-8192, 15.9 us instead of 14.3.)
-constexpr int kMergeRows = 8;
+// kMergeRows rows, as many lanes a row as it has 16-byte chunks and kRowSteps
+// rows per lane, so a load reads whole rows and every lane dims of the head.
+// The pieces come in batches of kBatch with all their loads in flight, under a
+// running max (each batch rescales the sums at most once).  (With 4 lanes a
+// row, 64 bytes each, a load touched a quarter of every line: 16 sequences of
+// 64/8 heads, prefixes 1024-8192, 15.9 us instead of 14.3.  With 16 lanes a row
+// for head size 64 as well, half of them read bytes that nobody wrote: 2
+// sequences of 64/8 heads, 15 and 26 nodes over prefixes of 240 and 469, a call
+// 18.6 us instead of 16.7; 32 of 8/2 heads, 12-31 nodes over 545-1909, 22.6
+// instead of 20.7.)
+template <int HD>
+constexpr int kMergeRows = HD == 64 ? 16 : 8;
 template <int HD>
 __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   constexpr int kBatch = 4;
-  constexpr int kRowSteps = kMergeRows / 4;
+  constexpr int kRowLanes = HD / 8;             // lanes of a row
+  constexpr int kStepRows = kWave / kRowLanes;  // rows of a step
+  constexpr int kRowSteps = kMergeRows<HD> / kStepRows;
   if (halted(a.status)) return;
   const int units = *reinterpret_cast<const int32_t*>(a.ws_desc);
   const MergeDesc d = a.ws_desc[1 + blockIdx.x];
@@ -1357,12 +1364,12 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   const int wv = threadIdx.x / kWave;
   const int lane = threadIdx.x % kWave;
   const int rows = min(a.G * d.n - d.rt * kTileRows, kTileRows);
-  const int r0 = (blockIdx.y * 4 + wv) * kMergeRows;
+  const int r0 = (blockIdx.y * 4 + wv) * kMergeRows<HD>;
   if (r0 >= rows) return;
-  const int col = lane & 15;
+  const int col = lane % kRowLanes;
   int r[kRowSteps];  // (rows past the unit's compute its last, unstored)
 #pragma unroll
-  for (int i = 0; i < kRowSteps; ++i) r[i] = min(r0 + 4 * i + (lane >> 4), rows - 1);
+  for (int i = 0; i < kRowSteps; ++i) r[i] = min(r0 + kStepRows * i + lane / kRowLanes, rows - 1);
   const int npieces = d.pieces;
   // Slot of piece k: its place alone when every range holds an item of the
   // unit, else (calls with fewer items than workgroups, as when Nmax is far
@@ -1432,7 +1439,7 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   }
 #pragma unroll
   for (int i = 0; i < kRowSteps; ++i) {
-    if (r0 + 4 * i + (lane >> 4) >= rows || col >= HD / 8) continue;
+    if (r0 + kStepRows * i + lane / kRowLanes >= rows) continue;
     const float inv = 1.f / wsum[i];
     const int row = d.rt * kTileRows + r[i];  // stacked row = node * G + head in group
     const int node = node_of(a, row);
@@ -1732,10 +1739,10 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
   if (e != hipSuccess) return e;
   // One merge workgroup column per possible unit, 4 * kMergeRows rows per workgroup.
   if (s.d == 64)
-    hipLaunchKernelGGL(attn_stream_merge_kernel<64>, dim3(a.max_units, kTileRows / (4 * kMergeRows)), dim3(256),
+    hipLaunchKernelGGL(attn_stream_merge_kernel<64>, dim3(a.max_units, kTileRows / (4 * kMergeRows<64>)), dim3(256),
                        0, stream, a);
   else
-    hipLaunchKernelGGL(attn_stream_merge_kernel<128>, dim3(a.max_units, kTileRows / (4 * kMergeRows)), dim3(256),
+    hipLaunchKernelGGL(attn_stream_merge_kernel<128>, dim3(a.max_units, kTileRows / (4 * kMergeRows<128>)), dim3(256),
                        0, stream, a);
   return hipGetLastError();
 }
