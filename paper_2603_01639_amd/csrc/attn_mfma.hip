@@ -1349,14 +1349,12 @@ __global__ void __launch_bounds__(kThreads, 1) attn_stream_kernel(MfmaArgs a) {
 // sequences of 64/8 heads, 15 and 26 nodes over prefixes of 240 and 469, a call
 // 18.6 us instead of 16.7; 32 of 8/2 heads, 12-31 nodes over 545-1909, 22.6
 // instead of 20.7.)
-template <int HD>
-constexpr int kMergeRows = HD == 64 ? 16 : 8;
-template <int HD>
+template <int HD, int kMergeRows>
 __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   constexpr int kBatch = 4;
   constexpr int kRowLanes = HD / 8;             // lanes of a row
   constexpr int kStepRows = kWave / kRowLanes;  // rows of a step
-  constexpr int kRowSteps = kMergeRows<HD> / kStepRows;
+  constexpr int kRowSteps = kMergeRows / kStepRows;
   if (halted(a.status)) return;
   const int units = *reinterpret_cast<const int32_t*>(a.ws_desc);
   const MergeDesc d = a.ws_desc[1 + blockIdx.x];
@@ -1364,7 +1362,7 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   const int wv = threadIdx.x / kWave;
   const int lane = threadIdx.x % kWave;
   const int rows = min(a.G * d.n - d.rt * kTileRows, kTileRows);
-  const int r0 = (blockIdx.y * 4 + wv) * kMergeRows<HD>;
+  const int r0 = (blockIdx.y * 4 + wv) * kMergeRows;
   if (r0 >= rows) return;
   const int col = lane % kRowLanes;
   int r[kRowSteps];  // (rows past the unit's compute its last, unstored)
@@ -1458,6 +1456,7 @@ namespace {
 
 constexpr int kMinTilesPerWg = 2;   // a share shorter than this is mostly fixed cost
 constexpr int kMaxGrid = 1024;      // workgroups of the attention grid at most
+constexpr int kWideMerge = 2048;    // stream merge: units from which a wave takes 16 rows
 
 // Stacked-row tiles and key tiles of the longest unit the launch allows.
 int64_t max_unit_tiles(const AttnShape& s) {
@@ -1737,13 +1736,20 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
   });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // One merge workgroup column per possible unit, 4 * kMergeRows rows per workgroup.
-  if (s.d == 64)
-    hipLaunchKernelGGL(attn_stream_merge_kernel<64>, dim3(a.max_units, kTileRows / (4 * kMergeRows<64>)), dim3(256),
-                       0, stream, a);
-  else
-    hipLaunchKernelGGL(attn_stream_merge_kernel<128>, dim3(a.max_units, kTileRows / (4 * kMergeRows<128>)), dim3(256),
-                       0, stream, a);
+  // One merge workgroup column per possible unit, 4 * rows of its rows per
+  // workgroup.  At most W - 1 units are cut, so in a wide table most workgroups
+  // only read an entry, and fewer of them cost less; in a narrow one more of
+  // them hide more of the loads.  Head size 128, 8 / 16 rows a wave: 32 units
+  // 25.8 / 30.2 us a call, 64 units 49.5 / 51.2, 512 units 261 / 259, 1536 units
+  // 39.3 / 40.2, 2048 units 42.9 / 40.8, 4096 units 86.6 / 80.0.
+  const auto launch_merge = [&](auto d, auto rows) {
+    hipLaunchKernelGGL((attn_stream_merge_kernel<d(), rows()>), dim3(a.max_units, kTileRows / (4 * rows())),
+                       dim3(256), 0, stream, a);
+  };
+  using Rows16 = std::integral_constant<int, 16>;
+  if (s.d == 64) launch_merge(std::integral_constant<int, 64>{}, Rows16{});
+  else if (a.max_units >= kWideMerge) launch_merge(std::integral_constant<int, 128>{}, Rows16{});
+  else launch_merge(std::integral_constant<int, 128>{}, std::integral_constant<int, 8>{});
   return hipGetLastError();
 }
 

@@ -11,12 +11,12 @@ import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-def _check(Hq, Hkv, d, prefix, nodes, Nmax):
+def _check(Hq, Hkv, d, prefix, nodes, Nmax, block=0):
     rng = np.random.default_rng(sum(nodes) + Hq + d)
     trees = [W.tree_uniform_parent(rng, n) for n in nodes]
     b = W.make_batch(rng, dtype=W.DTYPE_BF16, Hq=Hq, Hkv=Hkv, d=d, prefix=prefix, trees=trees,
                      tokens=[W.distinct_sibling_tokens(rng, t, 500) for t in trees], Voc=500, p_match=0.7,
-                     Nmax=Nmax, label=f"{Hq}/{Hkv} heads, d={d}, N={nodes}")
+                     Nmax=Nmax, block_size=block, label=f"{Hq}/{Hkv} heads, d={d}, N={nodes}")
     U.log(f"[stream merge] {b.label}")
     U.compare_attention(b, U.gpu_attention(b, U.upload(b)), U.oracle_attention(b))
 
@@ -25,3 +25,18 @@ def _check(Hq, Hkv, d, prefix, nodes, Nmax):
 @pytest.mark.parametrize("n", [1, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 127, 129, 255, 256])
 def test_rows(n, d):
     _check(1, 1, d, [1500, 700], [n, max(1, n - 1)], 256)
+
+
+@pytest.mark.parametrize("B", [127, 128])
+def test_wide_table(B):
+    """Both sides of the 2048 units (16 a sequence here) from which a wave of
+    the merge takes 16 rows of a 128-dim head."""
+    _check(64, 8, 128, [37 * (i % 7) for i in range(B)], [1 + (5 * i) % 33 for i in range(B)], 33)
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 13, 51, 52])
+def test_rows_of_a_wide_table(n):
+    """The row edges (5 rows a node) in a table of 2048 units of which few are
+    cut: two longer sequences, the others of one key."""
+    B = 128
+    _check(40, 8, 128, [900, 500] + [0] * (B - 2), [n, max(1, n - 1)] + [1] * (B - 2), 52, block=16)
