@@ -283,10 +283,10 @@ __device__ __forceinline__ LoadPlan make_load_plan(int wave, int lane) {
 // loop keeps only its own layout's addressing state in scalar registers (the
 // contiguous instantiation of the split kernel then spills none of them).
 // kKG is the number of key groups.  With one, wave w takes rows 32w .. 32w + 31
-// of the unit and all 64 keys of a tile.  With two (units of at most 128 rows),
-// waves 2r and 2r + 1 take rows 32r .. 32r + 31 and one 32-key half of every
-// tile each, and the pair's results are joined through LDS at the end: all 8
-// waves then work where half of them would only load tiles (32/8 heads, prefix
+// of the unit and all 64 keys of a tile.  With two (calls whose units have at most
+// 64 rows, two_key_groups), waves 2r and 2r + 1 take rows 32r .. 32r + 31 and
+// one 32-key half of every tile each, and the pair's results are joined through
+// LDS at the end: twice the waves then work on each tile (32/8 heads, prefix
 // 1196, 12 nodes, ten layers and acceptance 118.1 -> 115.7 us; 64/8 heads,
 // prefix 4096, 8 nodes 12.8 -> 12.0; 11 sequences of 56 rows 43.0 -> 42.0).
 template <bool kTree, int HD, bool kPaged, int kKG>
@@ -1528,15 +1528,23 @@ int64_t worst_split_key_cap(const AttnShape& s) {
   return split_key_cap(w);
 }
 
-// Two key groups when every unit of the call fits half of the waves.  (Mixed
-// calls stay with one: a choice per unit, with both loops in one kernel,
-// overran the instruction cache and lost 2-4% on batches of 32- to 220-row
-// units, where it gained 5-8% with all units of at most 128 rows.)
-bool two_key_groups(const AttnShape& s) { return s.Hq / s.Hkv * s.Nmax <= kTileRows / 2; }
+// Two key groups when every unit of the call fits two waves' rows.  A compute
+// unit has four SIMDs: with one group, units of 33 to 64 rows leave two of them
+// without work and shorter ones three, which the second group puts to use; from
+// 65 rows on the waves of one group already cover three or four SIMDs, and the
+// join costs more than it gives.  One group against two, a call: 32/8 heads,
+// 16 nodes (64 rows), prefix 128: 9.0 / 8.6 us, 4096: 12.2 / 12.1, 16384: 21.4 /
+// 20.3, 16 sequences of prefix 1024: 25.9 / 24.1; 24 nodes (96 rows): 9.0 / 10.1,
+// 12.4 / 13.8, 21.8 / 22.1 and 26.5 / 28.2; 32 nodes 9.0 / 10.5, 12.8 / 14.2,
+// 23.3 / 23.2 and 27.8 / 29.7.  Head size 64 and ungrouped queries have the line
+// in much the same place.  (Mixed calls stay with one group: a choice per unit, with
+// both loops in one kernel, overran the instruction cache and lost 2-4% on
+// batches of 32- to 220-row units.)
+bool two_key_groups(const AttnShape& s) { return s.Hq / s.Hkv * s.Nmax <= kTileRows / 4; }
 
 // Estimated time of a split plan, in key tiles of a 256-row unit (about 2 us).
-// `tile` is the cost of one key tile for the plan's units: a unit of at most
-// 128 rows works on each tile with two key groups.
+// `tile` is the cost of one key tile for the plan's units (less with two key
+// groups).
 static double plan_cost(int64_t P, int n, int64_t sk, bool alone, int64_t units, int64_t target, double tile) {
   constexpr double kFixedTiles = 3.0, kMaskTiles = 0.5, kMergeTiles = 2.5;
   const int64_t tps = sk / kKT;
@@ -1557,7 +1565,7 @@ static double plan_cost(int64_t P, int n, int64_t sk, bool alone, int64_t units,
          (S > 1 ? kMergeTiles + S / 32.0 : 0.0);
 }
 
-constexpr double kHalfTile = 0.55;  // a key tile's cost for a unit of at most 128 rows
+constexpr double kHalfTile = 0.55;  // a key tile's cost with two key groups
 
 void plan_split(const AttnShape& s, int num_cus, AttnPlan* p) {
   const int G = s.Hq / s.Hkv;

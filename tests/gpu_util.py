@@ -140,3 +140,44 @@ def check_compact(b: W.VerifyBatch, dev: DevBatch, acc, nacc):
     np.testing.assert_array_equal(new_len, want_len)
     np.testing.assert_array_equal(to_host(dev.k), k)
     np.testing.assert_array_equal(to_host(dev.v), v)
+
+
+def attention_call(b: W.VerifyBatch, max_prefix):
+    """The attention call on device copies of a batch, with a workspace full of
+    NaN, as a callable, and its output."""
+    torch = _torch()
+    dev = upload(b)
+    out = torch.zeros(tuple(b.q.shape), dtype=torch.bfloat16, device="cuda")
+    size = ltd.attn_workspace_size(b.B, b.Nmax, b.Hq, b.Hkv, b.d, max_prefix, b.dtype)
+    ws = torch.full((max(size, 1),), 0xFF, dtype=torch.uint8, device="cuda")
+
+    def run():
+        ltd.tree_verify_attn(dev.q, dev.k, dev.v, dev.prefix_len, dev.parents, dev.n_nodes, out,
+                             max_prefix=max_prefix, block_table=dev.block_table, num_blocks=b.num_blocks,
+                             workspace=ws)
+    return run, out
+
+
+def call_times(*calls, n=10, rounds=7):
+    """Fastest time of each call in us, in graphs of n replayed in turn."""
+    torch = _torch()
+    graphs = []
+    for run in calls:
+        run()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            for _ in range(n):
+                run()
+        g.replay()
+        graphs.append(g)
+    best = [float("inf")] * len(calls)
+    for _ in range(rounds):
+        for i, g in enumerate(graphs):
+            a, z = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            g.replay()
+            z.record()
+            z.synchronize()
+            best[i] = min(best[i], a.elapsed_time(z) * 1e3 / n)
+    return best

@@ -1,8 +1,8 @@
-"""Units of at most 128 stacked rows split each key tile between two groups of
-waves: both sides of that rule, every number of 32-row blocks, prefixes whose
-last tile leaves the second group (keys 32-63 of a tile) without a visible
-key, and a scale for which the untouched running max times the scale would
-overflow."""
+"""Calls whose units have at most 64 stacked rows split each key tile between two
+groups of waves: both sides of that rule, every number of 32-row blocks up to
+four, prefixes whose last tile leaves the second group (keys 32-63 of a tile)
+without a visible key, and a scale for which the untouched running max times the
+scale would overflow."""
 import numpy as np
 import pytest
 import torch
@@ -34,8 +34,8 @@ def _check(d, G, N, prefix, block=0, scale=None):
 
 
 @pytest.mark.parametrize("d", [128, 64])
-@pytest.mark.parametrize("G,N", [(1, 1), (1, 33), (4, 8), (4, 9), (4, 16), (8, 12), (4, 32), (5, 25), (5, 26),
-                                 (1, 128), (1, 129)])
+@pytest.mark.parametrize("G,N", [(1, 1), (1, 33), (4, 8), (4, 9), (8, 8), (4, 16), (1, 64), (1, 65), (5, 12),
+                                 (5, 13), (4, 17), (8, 12), (4, 32), (5, 25), (5, 26), (1, 128), (1, 129)])
 def test_row_counts(G, N, d):
     _check(d, G, N, [97])
     _check(d, G, N, [300, 64, 1], block=16)
@@ -50,3 +50,19 @@ def test_partial_tiles(P):
 @pytest.mark.parametrize("P", [0, 1, 31, 65])
 def test_large_scale(P):
     _check(128, 4, 3, [P], scale=2.0)
+
+
+@pytest.mark.parametrize("P", [256, 1024])
+def test_time_of_four_row_blocks(P):
+    """Two groups of waves on 128 rows made a tree of 32 nodes slower than one
+    of 33, which needs a fifth block of rows."""
+    rng = np.random.default_rng(P)
+    calls = []
+    for n in (32, 33):
+        tree = W.tree_uniform_parent(rng, n)
+        b = W.make_batch(rng, dtype=W.DTYPE_BF16, Hq=32, Hkv=8, d=128, prefix=[P], trees=[tree],
+                         tokens=[W.distinct_sibling_tokens(rng, tree, 500)], Voc=500, p_match=0.7)
+        calls.append(U.attention_call(b, P)[0])
+    t = U.call_times(*calls)
+    U.log(f"[key groups] P={P}: 32 nodes {t[0]:.1f} us, 33 nodes {t[1]:.1f} us")
+    assert t[0] < t[1], t  # 1.16 and 1.03 times with two groups, 0.88 with one

@@ -4,10 +4,9 @@ with a workspace full of NaN so that a partial nobody wrote shows, and the
 time against the same call with tight bounds."""
 import numpy as np
 import pytest
-import torch
+import torch  # noqa: F401  (its HIP runtime is loaded before the library asks for the device)
 
 import gpu_util as U
-import oracle
 import paper_2603_01639_amd as ltd
 import workloads as W
 
@@ -22,49 +21,11 @@ def _batch(Hq, Hkv, d, prefix, nodes, Nmax, block=0):
                         Nmax=Nmax, block_size=block, label=f"d={d} P={prefix} N={nodes} Nmax={Nmax}")
 
 
-def _call(b, max_prefix):
-    """The call on device copies, its output and a workspace of NaN."""
-    dev = U.upload(b)
-    out = torch.zeros(tuple(b.q.shape), dtype=torch.bfloat16, device="cuda")
-    size = ltd.attn_workspace_size(b.B, b.Nmax, b.Hq, b.Hkv, b.d, max_prefix, b.dtype)
-    ws = torch.full((max(size, 1),), 0xFF, dtype=torch.uint8, device="cuda")
-
-    def run():
-        ltd.tree_verify_attn(dev.q, dev.k, dev.v, dev.prefix_len, dev.parents, dev.n_nodes, out,
-                             max_prefix=max_prefix, block_table=dev.block_table, num_blocks=b.num_blocks,
-                             workspace=ws)
-    return run, out
-
-
 def _check(b, max_prefix):
     U.log(f"[loose bounds] {b.label} max_prefix={max_prefix}")
-    run, out = _call(b, max_prefix)
+    run, out = U.attention_call(b, max_prefix)
     run()
     U.compare_attention(b, U.to_host(out), U.oracle_attention(b))
-
-
-def _times(*calls, n=10, rounds=7):
-    """Fastest time of each call in us, in graphs of n replayed in turn."""
-    graphs = []
-    for run in calls:
-        run()
-        torch.cuda.synchronize()
-        g = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(g):
-            for _ in range(n):
-                run()
-        g.replay()
-        graphs.append(g)
-    best = [float("inf")] * len(calls)
-    for _ in range(rounds):
-        for i, g in enumerate(graphs):
-            a, z = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            a.record()
-            g.replay()
-            z.record()
-            z.synchronize()
-            best[i] = min(best[i], a.elapsed_time(z) * 1e3 / n)
-    return best
 
 
 @pytest.mark.parametrize("d", [128, 64])
@@ -80,8 +41,8 @@ def test_time_of_sparse_pieces():
     """A merge that looks its pieces up one by one took this call from 22.6 to
     38.5 us; with tight bounds it has few pieces."""
     prefix, nodes = [711, 711], [4, 2]
-    loose, tight = (_call(_batch(8, 1, 64, prefix, nodes, n), 711)[0] for n in (256, 4))
-    t = _times(loose, tight)
+    loose, tight = (U.attention_call(_batch(8, 1, 64, prefix, nodes, n), 711)[0] for n in (256, 4))
+    t = U.call_times(loose, tight)
     U.log(f"[loose bounds] Nmax 256: {t[0]:.1f} us, Nmax 4: {t[1]:.1f} us")
     assert t[0] < 2.5 * t[1], t  # 3.3 one by one, 2.0 by lanes
 
@@ -108,6 +69,6 @@ def test_time_of_a_loose_prefix_bound():
     """A merge that requests every planned split's rows took this call from 101
     to 153 us; with max_prefix tight it takes 41."""
     b = _batch(64, 8, 128, [2225, 5070, 3000, 4000], [14, 42, 20, 30], 256, block=16)
-    t = _times(_call(b, 81120)[0], _call(b, 5070)[0])
+    t = U.call_times(U.attention_call(b, 81120)[0], U.attention_call(b, 5070)[0])
     U.log(f"[loose bounds] max_prefix 81120: {t[0]:.1f} us, 5070: {t[1]:.1f} us")
     assert t[0] < 2.5 * t[1], t  # 3.7 with every planned split requested, 1.7 without
