@@ -323,8 +323,8 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
 
   // ---- Q rows and parent links, straight into LDS ahead of everything else
   // (the tile loads queue behind them, and the wait for them below leaves the
-  // first tiles in flight).  Wave w's 32 stacked rows row0 + 32w + R land at
-  // 256*R in its 8 KiB block, with 16-byte chunk c at c ^ (R & 15), the
+  // first tiles in flight).  A wave's 32 stacked rows row0 + 32 rb + R (its own,
+  // or with two key groups its pair's) land at 256*R in its 8 KiB block, with 16-byte chunk c at c ^ (R & 15), the
   // layout the K operand also uses; rows past valid_rows repeat the last
   // valid row (their results are never stored).
   const int qrow_idx = row0 + rb * 32 + l32;
@@ -1211,7 +1211,7 @@ __global__ void __launch_bounds__(256) attn_split_merge_few_kernel(MfmaArgs a) {
   const int b = bg / a.Hkv;
   const int g = bg % a.Hkv;
   if (halted(a.status)) return;
-  const int row = blockIdx.y * 16 + threadIdx.x / 16;  // below row_tiles * kTileRows
+  const int row = blockIdx.y * 16 + threadIdx.x / 16;  // below row_tiles * tile_rows
   const int col = threadIdx.x % 16;
   const int Mpad = a.row_tiles * a.tile_rows;
   const int64_t part0 = static_cast<int64_t>(bg) * a.max_splits * Mpad + row;
@@ -1294,7 +1294,7 @@ __global__ void __launch_bounds__(kThreads, 1) attn_stream_kernel(MfmaArgs a) {
                                       sh.tree ? 1 : 0, whole ? 1 : 0, slot};
             ++k;
             if (sh.tree) {  // this workgroup owns the unit's last item: its merge entry
-              const plan::MergeJob job = plan::unit_job(q, u, U, s, gr, find);
+              const plan::MergeJob job = plan::unit_job(q, u, U, s, gr);
               if (threadIdx.x == 0) {
                 MergeDesc d{};
                 d.active = job.active;

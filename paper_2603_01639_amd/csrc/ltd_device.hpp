@@ -87,9 +87,6 @@ __device__ __forceinline__ float wave_max_dpp(float v) {
 __device__ __forceinline__ float wave_sum_dpp(float v) {
   return wave_reduce(v, [](float x, float y) { return x + y; });
 }
-__device__ __forceinline__ float rows_sum_dpp(float v) {
-  return rows_reduce(v, [](float x, float y) { return x + y; });
-}
 
 // Element offset of logical cache row `row` of sequence b, kv head g.
 // Contiguous: [B][Hkv][kv_rows][d]; paged: [num_blocks][Hkv][kv_rows][d]

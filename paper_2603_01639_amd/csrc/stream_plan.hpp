@@ -39,8 +39,10 @@ constexpr int kUnitRows = 256;  // stacked query rows per unit (8 waves x 32)
 constexpr int kWaveRows = 32;
 
 // Relative cost of one key tile for a row tile with v busy waves (measured
-// with per-workgroup timestamps on a batch of 16 sequences: about 2.3 us per
-// tile with 5-8 waves, 1.6 us with 1-4).
+// with per-workgroup timestamps on a batch of 16 sequences with one key group:
+// about 2.3 us per tile with 5-8 waves, 1.6 us with 1-4; these figures and the two
+// below were not taken again for calls with two key groups, whose units have 1
+// or 2 blocks of rows and so all weigh the same).
 constexpr int tile_weight(int waves) { return waves >= 5 ? 3 : 2; }
 // Axis extent of a tree key tile in prefix tiles (the ancestor masks are built
 // and applied on them: about 6.5 us per tree tile with 5-8 waves), and of a
@@ -198,10 +200,6 @@ constexpr int unit_index(const SeqAt& q, const Unit& u) { return q.ubase + u.g *
 constexpr int64_t unit_end(const SeqAt& q, const Unit& u) {
   return q.pre + u.start + static_cast<int64_t>(u.w) * unit_extent(q.c.t_pre, q.c.t_tree);
 }
-// Axis position of a unit's tree block (its last item).
-constexpr int64_t tree_item(int64_t U, int w, int t_pre) {
-  return first_item(U, w) + static_cast<int64_t>(w) * t_pre;
-}
 
 // Workgroup s's shares, in order, from axis position `pos` (its range start,
 // or where an earlier call stopped): visit(seq, unit, U, share, whole, slot)
@@ -252,10 +250,7 @@ struct MergeJob {
   bool dense;
 };
 
-// (`find` is not called: a unit's slots follow from its pieces' places in it.)
-template <class Find>
-constexpr MergeJob unit_job(const SeqAt& q, const Unit& u, int64_t U, int s, const Grid& gr,
-                            const Find&) {
+constexpr MergeJob unit_job(const SeqAt& q, const Unit& u, int64_t U, int s, const Grid& gr) {
   MergeJob j{};
   j.q = q;
   j.u = u;

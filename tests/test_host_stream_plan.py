@@ -122,7 +122,7 @@ int main() {
         if (jobs.count(U) || indices.count(ui)) bad = true;
         jobs[U] = s;
         indices.insert(ui);
-        const MergeJob j = unit_job(q, u, U, s, gr, find);
+        const MergeJob j = unit_job(q, u, U, s, gr);
         if (j.active == whole) bad = true;
         std::vector<std::pair<int, int>> got;
         if (j.active)
