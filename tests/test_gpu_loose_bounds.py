@@ -52,7 +52,8 @@ def test_time_of_sparse_pieces():
 # heads, plans of 4 and 20 whose partials are not requested before the lengths
 # are known.
 @pytest.mark.parametrize("d", [128, 64])
-@pytest.mark.parametrize("Hq,Hkv,Nmax,max_prefix,lo,hi", [(8, 2, 31, 640, 2, 8), (8, 2, 31, 2200, 9, 32),
+@pytest.mark.parametrize("Hq,Hkv,Nmax,max_prefix,lo,hi", [(8, 2, 16, 640, 2, 8), (8, 2, 16, 2200, 9, 32),
+                                                          (8, 2, 31, 640, 2, 8), (8, 2, 31, 2200, 9, 32),
                                                           (8, 2, 31, 6300, 33, 64), (64, 8, 256, 6000, 2, 8),
                                                           (64, 8, 256, 40000, 9, 32)])
 def test_fewer_splits_than_planned(Hq, Hkv, Nmax, max_prefix, lo, hi, d):

@@ -1,6 +1,7 @@
 """The split plan's merge kernels on both sides of the rule that picks between
-them (at most 8 splits: 16 lanes a row; more: a wave a row) and of the splits
-the wave kernel requests up front (32) and weights per lane (64)."""
+them (at most 8 splits: 16 lanes a row; more: a wave a row), of the splits
+the wave kernel requests up front (32) and of the splits it weights per lane
+(64), for units of 128 rows (two key groups) and of 256 rows (one)."""
 import numpy as np
 import pytest
 import torch  # noqa: F401  (its HIP runtime is loaded before the library asks for the device)
@@ -13,27 +14,27 @@ pytestmark = pytest.mark.gpu
 
 
 def _prefix_with_splits(splits, N, Hq, Hkv, d):
-    """The shortest prefix that one sequence's plan cuts into `splits` pieces or
-    more (the plan skips some counts)."""
+    """The shortest prefix that one sequence's plan cuts into exactly `splits`
+    pieces."""
     def grid(P):
         return ltd.attn_grid(1, N, Hq, Hkv, d, P, ltd.DTYPE_BF16, P + N)
     units = grid(1)
-    for P in range(65, 12000, 16):
-        if grid(P) >= units * splits:
+    for P in range(65, 14000, 16):
+        if grid(P) == units * splits:
             return P
     pytest.fail(f"no prefix gives {splits} splits")
 
 
 @pytest.mark.parametrize("d", [128, 64])
-@pytest.mark.parametrize("splits", [3, 8, 9, 32, 33, 64, 65])
-def test_split_counts(splits, d):
-    Hq, Hkv, N = 8, 2, 31  # 124 rows: one row tile
+@pytest.mark.parametrize("N,splits", [(33, 3)] + [(N, s) for N in (16, 33) for s in (8, 9, 32, 33, 63, 64, 65)])
+def test_split_counts(N, splits, d):
+    Hq, Hkv = 8, 2  # 4 rows a node
     P = _prefix_with_splits(splits, N, Hq, Hkv, d)
     rng = np.random.default_rng(splits * 2 + d)
     tree = W.tree_uniform_parent(rng, N)
     b = W.make_batch(rng, dtype=W.DTYPE_BF16, Hq=Hq, Hkv=Hkv, d=d, prefix=[P], trees=[tree],
-                     tokens=[W.distinct_sibling_tokens(rng, tree, 500)], Voc=500, p_match=0.7, Nmax=N + 1,
-                     label=f"{splits} splits")
-    U.log(f"[merge] splits={splits} d={d} P={P}")
+                     tokens=[W.distinct_sibling_tokens(rng, tree, 500)], Voc=500, p_match=0.7, Nmax=N,
+                     label=f"{splits} splits, {4 * N} rows")
+    U.log(f"[merge] splits={splits} d={d} N={N} P={P}")
     got = U.gpu_attention(b, U.upload(b))
     U.compare_attention(b, got, U.oracle_attention(b))
