@@ -117,7 +117,6 @@ struct MfmaArgs {
   // the tree may take a split of its own, row tiles per (sequence, kv head)
   int split_keys, max_splits, tree_alone, row_tiles;
   int tile_rows;  // stacked rows per unit
-  int merge_early;  // split plan: the merge requests partials before it knows the sequence's lengths
   float scale_log2;
   float lazy_gap;  // kLazyMax / scale_log2: the raw-score margin of the lazy max
 };
@@ -1088,11 +1087,11 @@ __device__ __forceinline__ int merge_splits(const MfmaArgs& a, int b, int row) {
 // load, and the groups' sums are added with two lane exchanges.  A small
 // launch is latency-bound, so the (m, l) pairs and the first 32 splits' rows are
 // then requested before the sequence's prefix length and node count arrive
-// (merge_early): every row of the grid is inside the workspace's Mpad rows, and
+// (kEarly): every row of the grid is inside the workspace's Mpad rows, and
 // every split index below max_splits inside its splits.  (A second round for the splits past 16
 // and reductions through the LDS crossbar made it 5.0 us instead of 4.1 for
 // 240 rows of 17 splits on 8 kv heads.)
-template <int HD>
+template <int HD, bool kEarly>
 __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
   __shared__ float w_s[4][kMaxMergeSplits];
   constexpr int kFirst = 32;  // splits whose rows are requested up front
@@ -1109,7 +1108,7 @@ __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
   const unsigned char* op = reinterpret_cast<const unsigned char*>(a.ws_o + part0 * kD) + col * 16;
   const int64_t stride = static_cast<int64_t>(Mpad) * kD * 2;  // bytes between splits
   int live = a.max_splits;  // splits whose partials are read
-  if (!a.merge_early) {
+  if constexpr (!kEarly) {
     live = merge_splits(a, b, row);
     if (live <= 1) return;
   }
@@ -1122,7 +1121,7 @@ __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
     o0[u] = sp < live ? *reinterpret_cast<const u32x4*>(op + sp * stride)
                       : (u32x4){0u, 0u, 0u, 0u};
   }
-  const int n_splits = a.merge_early ? merge_splits(a, b, row) : live;
+  const int n_splits = kEarly ? merge_splits(a, b, row) : live;
   if (n_splits <= 1) return;
   float M = lane < n_splits ? ml0.x : -INFINITY;
   for (int s = lane + kWave; s < n_splits; s += kWave) M = fmaxf(M, a.ws_ml[(part0 + s * Mpad) * 2]);
@@ -1205,7 +1204,7 @@ constexpr int kFewSplits = 8;
 // max_prefix 81120 and Nmax 256, 671 MB: 153 us, now 69.5).  At 17 MB (64/8 heads,
 // prefix 4096, 256 nodes) the two are alike.
 constexpr size_t kEarlyMergeBytes = size_t{16} << 20;
-template <int HD>
+template <int HD, bool kEarly>
 __global__ void __launch_bounds__(256) attn_split_merge_few_kernel(MfmaArgs a) {
   const int bg = blockIdx.x;
   const int b = bg / a.Hkv;
@@ -1216,7 +1215,7 @@ __global__ void __launch_bounds__(256) attn_split_merge_few_kernel(MfmaArgs a) {
   const int Mpad = a.row_tiles * a.tile_rows;
   const int64_t part0 = static_cast<int64_t>(bg) * a.max_splits * Mpad + row;
   int live = a.max_splits;  // splits whose partials are read
-  if (!a.merge_early) {
+  if constexpr (!kEarly) {
     live = merge_splits(a, b, row);
     if (live <= 1) return;
   }
@@ -1232,7 +1231,7 @@ __global__ void __launch_bounds__(256) attn_split_merge_few_kernel(MfmaArgs a) {
       o[s] = *reinterpret_cast<const u32x4*>(a.ws_o + r * kD + col * 8);
     }
   }
-  const int n_splits = a.merge_early ? merge_splits(a, b, row) : live;
+  const int n_splits = kEarly ? merge_splits(a, b, row) : live;
   if (n_splits <= 1) return;
   float M = -INFINITY;
 #pragma unroll
@@ -1708,7 +1707,6 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
     a.tile_rows = p.tile_rows;
     const size_t slots = static_cast<size_t>(s.B) * s.Hkv * p.max_splits * p.row_tiles * p.tile_rows;
     a.ws_ml = reinterpret_cast<float*>(ws + slots * kD * 2);
-    a.merge_early = slots * kD * 2 <= kEarlyMergeBytes ? 1 : 0;
     const dim3 grid(s.B * s.Hkv, p.row_tiles, p.max_splits);
     pick_kernel(s, a.block_table != nullptr, [&](auto d, auto paged, auto kg) {
       hipLaunchKernelGGL((attn_split_kernel<d(), paged(), kg()>), grid, dim3(kThreads), 0, stream, a);
@@ -1718,19 +1716,20 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
     // (sequence, kv head) fastest, as for the attention grid: a head's merge
     // runs on the XCD whose workgroups wrote its partials.
     const unsigned mrows = static_cast<unsigned>(p.row_tiles * p.tile_rows);
-    if (p.max_splits <= kFewSplits) {
-      const dim3 fgrid(s.B * s.Hkv, mrows / 16);
-      if (s.d == 64)
-        hipLaunchKernelGGL(attn_split_merge_few_kernel<64>, fgrid, dim3(256), 0, stream, a);
+    const auto launch_merge = [&](auto d, auto early) {
+      if (p.max_splits <= kFewSplits)
+        hipLaunchKernelGGL((attn_split_merge_few_kernel<d(), early()>), dim3(s.B * s.Hkv, mrows / 16), dim3(256),
+                           0, stream, a);
       else
-        hipLaunchKernelGGL(attn_split_merge_few_kernel<128>, fgrid, dim3(256), 0, stream, a);
-      return hipGetLastError();
-    }
-    const dim3 mgrid(s.B * s.Hkv, mrows / 4);
-    if (s.d == 64)
-      hipLaunchKernelGGL(attn_split_merge_kernel<64>, mgrid, dim3(256), 0, stream, a);
-    else
-      hipLaunchKernelGGL(attn_split_merge_kernel<128>, mgrid, dim3(256), 0, stream, a);
+        hipLaunchKernelGGL((attn_split_merge_kernel<d(), early()>), dim3(s.B * s.Hkv, mrows / 4), dim3(256), 0,
+                           stream, a);
+    };
+    const auto with_early = [&](auto d) {
+      if (slots * kD * 2 <= kEarlyMergeBytes) launch_merge(d, std::true_type{});
+      else launch_merge(d, std::false_type{});
+    };
+    if (s.d == 64) with_early(std::integral_constant<int, 64>{});
+    else with_early(std::integral_constant<int, 128>{});
     return hipGetLastError();
   }
   const size_t slots = static_cast<size_t>(2) * p.grid * kTileRows;
