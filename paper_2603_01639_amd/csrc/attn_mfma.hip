@@ -89,6 +89,7 @@ constexpr int kSchedMfma = 0x008, kSchedDsRead = 0x100;  // sched_group_barrier 
 constexpr int kKAhead = 2;                // k-steps of K fragments in flight
 constexpr int kMaxSplitTiles = 32;        // split plan: longest split in key tiles
 constexpr int kMaxMergeSplits = 1024;     // split plan: splits the merge takes at most
+constexpr int kMaxGrid = 1024;            // stream plan: workgroups at most, so pieces of a unit too
 constexpr int kTileRows = kWaves * 32;    // stacked query rows per workgroup (one unit)
 static_assert(kTileRows == plan::kUnitRows && kKT == plan::kKeyTile, "unit shape");
 
@@ -1351,6 +1352,7 @@ __global__ void __launch_bounds__(kThreads, 1) attn_stream_kernel(MfmaArgs a) {
 template <int HD, int kMergeRows>
 __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   constexpr int kBatch = 4;
+  __shared__ int16_t slot_s[256 / kWave][kMaxGrid];  // a sparse unit's piece slots, or -1
   constexpr int kRowLanes = HD / 8;             // lanes of a row
   constexpr int kStepRows = kWave / kRowLanes;  // rows of a step
   constexpr int kRowSteps = kMergeRows / kStepRows;
@@ -1358,7 +1360,7 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   const int units = *reinterpret_cast<const int32_t*>(a.ws_desc);
   const MergeDesc d = a.ws_desc[1 + blockIdx.x];
   if (static_cast<int>(blockIdx.x) >= units || !d.active) return;
-  const int wv = threadIdx.x / kWave;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = threadIdx.x % kWave;
   const int rows = min(a.G * d.n - d.rt * kTileRows, kTileRows);
   const int r0 = (blockIdx.y * 4 + wv) * kMergeRows;
@@ -1367,22 +1369,25 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
   int r[kRowSteps];  // (rows past the unit's compute its last, unstored)
 #pragma unroll
   for (int i = 0; i < kRowSteps; ++i) r[i] = min(r0 + kStepRows * i + lane / kRowLanes, rows - 1);
-  const int npieces = d.pieces;
-  // Slot of piece k: its place alone when every range holds an item of the
-  // unit, else (calls with fewer items than workgroups, as when Nmax is far
-  // above the trees' sizes) looked up in the partition.  A lookup is long, so
-  // the lanes take 64 pieces' at once (one by one: sequences of 2 and 4 nodes
-  // over prefixes of 711, one kv head, Nmax 256, 38.5 us a call; now 23.3).
-  auto slot_of = [&](int k) -> int {
-    if (k >= npieces) return -1;
-    if (d.dense) return plan::dense_piece_slot(d.sa, k);
+  const int npieces = min(d.pieces, kMaxGrid);
+  // A piece's slot follows from its place alone when every range holds an item
+  // of the unit (dense).  In calls with fewer items than workgroups, as when Nmax
+  // is far above the trees' sizes, it is looked up in the partition.  A lookup is
+  // long, so the lanes take 64 pieces' at once (one by one: sequences of 2 and 4
+  // nodes over prefixes of 711, one kv head, Nmax 256, 38.5 us a call; now 23.3);
+  // the slots wait in LDS, as one register more leaves room for five waves a
+  // SIMD instead of six.
+  if (!d.dense) {
     plan::MergeJob job{};
     job.sa = d.sa;
     job.U = d.U;
     job.u.w = d.w;
     job.q.c.t_pre = d.t_pre;
-    return plan::merge_piece_slot(job, k, plan::make_grid(d.C, a.W));
-  };
+    const plan::Grid gr = plan::make_grid(d.C, a.W);
+    for (int k = lane; k < npieces; k += kWave)
+      slot_s[wv][k] = static_cast<int16_t>(plan::merge_piece_slot(job, k, gr));
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  }
   float acc[kRowSteps][8] = {};
   float wsum[kRowSteps], M[kRowSteps];  // running max: acc and wsum are relative to 2^M
 #pragma unroll
@@ -1390,50 +1395,52 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
     wsum[i] = 0.f;
     M[i] = -INFINITY;
   }
-  int my_slot = -1;  // of piece k0 - k0 % 64 + lane
-  for (int k0 = 0; k0 < npieces; k0 += kBatch) {
-    if (k0 % kWave == 0) my_slot = slot_of(k0 + lane);
-    f32x2 ml[kRowSteps][kBatch];
-    u32x4 o[kRowSteps][kBatch];
-#pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      const int slot = __builtin_amdgcn_readlane(my_slot, (k0 + j) % kWave);
-#pragma unroll
-      for (int i = 0; i < kRowSteps; ++i) {
-        ml[i][j] = (f32x2){-INFINITY, 0.f};
-        o[i][j] = (u32x4){0u, 0u, 0u, 0u};
-        if (slot >= 0) {
-          const int64_t row = static_cast<int64_t>(slot) * kTileRows + r[i];
-          ml[i][j] = *reinterpret_cast<const f32x2*>(a.ws_ml + row * 2);
-          o[i][j] = *reinterpret_cast<const u32x4*>(a.ws_o + row * kD + col * 8);
-        }
-      }
-    }
-    // the batch's pieces join the running sums (one rescale per batch)
-#pragma unroll
-    for (int i = 0; i < kRowSteps; ++i) {
-      float Mb = M[i];
-#pragma unroll
-      for (int j = 0; j < kBatch; ++j) Mb = fmaxf(Mb, ml[i][j].x);
-      if (Mb > M[i]) {
-        const float alpha = M[i] == -INFINITY ? 0.f : exp2_fast(M[i] - Mb);
-        wsum[i] *= alpha;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[i][e] *= alpha;
-        M[i] = Mb;
-      }
+  auto fold_pieces = [&](auto slot_of) {
+    for (int k0 = 0; k0 < npieces; k0 += kBatch) {
+      f32x2 ml[kRowSteps][kBatch];
+      u32x4 o[kRowSteps][kBatch];
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) {
-        const float w = ml[i][j].y > 0.f ? exp2_fast(ml[i][j].x - M[i]) * ml[i][j].y : 0.f;
-        wsum[i] += w;
+        const int slot = k0 + j < npieces ? slot_of(k0 + j) : -1;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          acc[i][2 * e] += w * bf16_to_f32(static_cast<uint16_t>(o[i][j][e] & 0xFFFFu));
-          acc[i][2 * e + 1] += w * bf16_to_f32(static_cast<uint16_t>(o[i][j][e] >> 16));
+        for (int i = 0; i < kRowSteps; ++i) {
+          ml[i][j] = (f32x2){-INFINITY, 0.f};
+          o[i][j] = (u32x4){0u, 0u, 0u, 0u};
+          if (slot >= 0) {
+            const int64_t row = static_cast<int64_t>(slot) * kTileRows + r[i];
+            ml[i][j] = *reinterpret_cast<const f32x2*>(a.ws_ml + row * 2);
+            o[i][j] = *reinterpret_cast<const u32x4*>(a.ws_o + row * kD + col * 8);
+          }
+        }
+      }
+      // the batch's pieces join the running sums (one rescale per batch)
+#pragma unroll
+      for (int i = 0; i < kRowSteps; ++i) {
+        float Mb = M[i];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) Mb = fmaxf(Mb, ml[i][j].x);
+        if (Mb > M[i]) {
+          const float alpha = M[i] == -INFINITY ? 0.f : exp2_fast(M[i] - Mb);
+          wsum[i] *= alpha;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[i][e] *= alpha;
+          M[i] = Mb;
+        }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+          const float w = ml[i][j].y > 0.f ? exp2_fast(ml[i][j].x - M[i]) * ml[i][j].y : 0.f;
+          wsum[i] += w;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            acc[i][2 * e] += w * bf16_to_f32(static_cast<uint16_t>(o[i][j][e] & 0xFFFFu));
+            acc[i][2 * e + 1] += w * bf16_to_f32(static_cast<uint16_t>(o[i][j][e] >> 16));
+          }
         }
       }
     }
-  }
+  };
+  if (d.dense) fold_pieces([&](int k) { return plan::dense_piece_slot(d.sa, k); });
+  else fold_pieces([&](int k) { return __builtin_amdgcn_readfirstlane(static_cast<int>(slot_s[wv][k])); });
 #pragma unroll
   for (int i = 0; i < kRowSteps; ++i) {
     if (r0 + kStepRows * i + lane / kRowLanes >= rows) continue;
@@ -1454,7 +1461,6 @@ __global__ void __launch_bounds__(256) attn_stream_merge_kernel(MfmaArgs a) {
 namespace {
 
 constexpr int kMinTilesPerWg = 2;   // a share shorter than this is mostly fixed cost
-constexpr int kMaxGrid = 1024;      // workgroups of the attention grid at most
 constexpr int kWideMerge = 2048;    // stream merge: units from which a wave takes 16 rows
 
 // Stacked-row tiles and key tiles of the longest unit the launch allows.
@@ -1747,8 +1753,9 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
   // workgroup.  At most W - 1 units are cut, so in a wide table most workgroups
   // only read an entry, and fewer of them cost less; in a narrow one more of
   // them hide more of the loads.  Head size 128, 8 / 16 rows a wave: 32 units
-  // 25.8 / 30.2 us a call, 64 units 49.5 / 51.2, 512 units 261 / 259, 1536 units
-  // 39.3 / 40.2, 2048 units 42.9 / 40.8, 4096 units 86.6 / 80.0.
+  // 25.1 / 29.9 us a call, 64 units 49.6 / 52.4, 512 units 266 / 270, 1536 units
+  // 40.9 / 41.4, 2048 units 42.6 / 41.5, 4096 units 88.0 / 81.2, 8192 units 68.1 /
+  // 63.4.
   const auto launch_merge = [&](auto d, auto rows) {
     hipLaunchKernelGGL((attn_stream_merge_kernel<d(), rows()>), dim3(a.max_units, kTileRows / (4 * rows())),
                        dim3(256), 0, stream, a);
