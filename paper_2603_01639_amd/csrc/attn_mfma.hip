@@ -1755,15 +1755,18 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
   // them hide more of the loads.  Head size 128, 8 / 16 rows a wave: 32 units
   // 25.1 / 29.9 us a call, 64 units 49.6 / 52.4, 512 units 266 / 270, 1536 units
   // 40.9 / 41.4, 2048 units 42.6 / 41.5, 4096 units 88.0 / 81.2, 8192 units 68.1 /
-  // 63.4.
+  // 63.4.  Head size 64: 4 units 42.1 / 51.3 (many pieces: one row a lane keeps
+  // a batch's chain short), 128 units 18.7 / 20.8, 512 units 180.6 / 180.6.
   const auto launch_merge = [&](auto d, auto rows) {
     hipLaunchKernelGGL((attn_stream_merge_kernel<d(), rows()>), dim3(a.max_units, kTileRows / (4 * rows())),
                        dim3(256), 0, stream, a);
   };
-  using Rows16 = std::integral_constant<int, 16>;
-  if (s.d == 64) launch_merge(std::integral_constant<int, 64>{}, Rows16{});
-  else if (a.max_units >= kWideMerge) launch_merge(std::integral_constant<int, 128>{}, Rows16{});
-  else launch_merge(std::integral_constant<int, 128>{}, std::integral_constant<int, 8>{});
+  const auto with_rows = [&](auto d) {
+    if (a.max_units >= kWideMerge) launch_merge(d, std::integral_constant<int, 16>{});
+    else launch_merge(d, std::integral_constant<int, 8>{});
+  };
+  if (s.d == 64) with_rows(std::integral_constant<int, 64>{});
+  else with_rows(std::integral_constant<int, 128>{});
   return hipGetLastError();
 }
 
