@@ -1196,14 +1196,16 @@ __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
 // of 4 splits on 8 kv heads take 5.7 us here and 9.7 us there.  From 9 splits
 // on the rows are few, and a wave per row keeps more loads in flight.
 constexpr int kFewSplits = 8;
-// The launch's partial rows, in bytes, up to which the merges request them
-// before they know which were written.  Small merges wait on one round of
-// loads less (13.47 -> 13.35 us for 32/8 heads, prefix 2048, 60 nodes: 9 MB); in
+// The partials of a call's G * Nmax rows, in bytes, up to which the merges request
+// them before they know which were written.  Small merges wait on one round of
+// loads less (13.47 -> 13.35 us for 32/8 heads, prefix 2048, 60 nodes: 8 MB); in
 // large ones other waves hide the wait, and where max_prefix or Nmax is far above
 // the call's lengths the rows are mostly traffic for nothing (4 sequences of
 // 64/8 heads, 14-42 nodes, prefixes 2225-5070 in 16-row blocks under
 // max_prefix 81120 and Nmax 256, 671 MB: 153 us, now 69.5).  At 17 MB (64/8 heads,
-// prefix 4096, 256 nodes) the two are alike.
+// prefix 4096, 256 nodes) the two are alike.  (Padded rows are not counted nor
+// launched: 64/8 heads of 64 dims, prefix 10050, 11 nodes, 88 rows of 256: 14.4 us
+// with them, 12.9 without.)
 constexpr size_t kEarlyMergeBytes = size_t{16} << 20;
 template <int HD, bool kEarly>
 __global__ void __launch_bounds__(256) attn_split_merge_few_kernel(MfmaArgs a) {
@@ -1721,17 +1723,19 @@ hipError_t launch_attn_mfma(const AttnShape& s, const AttnPlan& p, const void* q
     if (e != hipSuccess || p.max_splits == 1) return e;  // one split: the output is final
     // (sequence, kv head) fastest, as for the attention grid: a head's merge
     // runs on the XCD whose workgroups wrote its partials.
-    const unsigned mrows = static_cast<unsigned>(p.row_tiles * p.tile_rows);
+    // (The call's rows, rounded up to a workgroup's below: still within Mpad.)
+    const unsigned mrows = static_cast<unsigned>(a.G * s.Nmax);
     const auto launch_merge = [&](auto d, auto early) {
       if (p.max_splits <= kFewSplits)
-        hipLaunchKernelGGL((attn_split_merge_few_kernel<d(), early()>), dim3(s.B * s.Hkv, mrows / 16), dim3(256),
+        hipLaunchKernelGGL((attn_split_merge_few_kernel<d(), early()>), dim3(s.B * s.Hkv, (mrows + 15) / 16), dim3(256),
                            0, stream, a);
       else
-        hipLaunchKernelGGL((attn_split_merge_kernel<d(), early()>), dim3(s.B * s.Hkv, mrows / 4), dim3(256), 0,
+        hipLaunchKernelGGL((attn_split_merge_kernel<d(), early()>), dim3(s.B * s.Hkv, (mrows + 3) / 4), dim3(256), 0,
                            stream, a);
     };
     const auto with_early = [&](auto d) {
-      if (slots * kD * 2 <= kEarlyMergeBytes) launch_merge(d, std::true_type{});
+      const size_t bytes = static_cast<size_t>(s.B) * s.Hkv * p.max_splits * mrows * kD * 2;
+      if (bytes <= kEarlyMergeBytes) launch_merge(d, std::true_type{});
       else launch_merge(d, std::false_type{});
     };
     if (s.d == 64) with_early(std::integral_constant<int, 64>{});

@@ -25,16 +25,28 @@ def _prefix_with_splits(splits, N, Hq, Hkv, d):
     pytest.fail(f"no prefix gives {splits} splits")
 
 
+def _check(Hq, Hkv, N, d, P, label):
+    rng = np.random.default_rng(N * 7 + P + d)
+    tree = W.tree_uniform_parent(rng, N)
+    b = W.make_batch(rng, dtype=W.DTYPE_BF16, Hq=Hq, Hkv=Hkv, d=d, prefix=[P], trees=[tree],
+                     tokens=[W.distinct_sibling_tokens(rng, tree, 500)], Voc=500, p_match=0.7, Nmax=N, label=label)
+    U.log(f"[merge] {label} d={d} P={P}")
+    got = U.gpu_attention(b, U.upload(b))
+    U.compare_attention(b, got, U.oracle_attention(b))
+
+
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("N,splits", [(33, 3)] + [(N, s) for N in (16, 33) for s in (8, 9, 32, 33, 63, 64, 65)])
 def test_split_counts(N, splits, d):
     Hq, Hkv = 8, 2  # 4 rows a node
     P = _prefix_with_splits(splits, N, Hq, Hkv, d)
-    rng = np.random.default_rng(splits * 2 + d)
-    tree = W.tree_uniform_parent(rng, N)
-    b = W.make_batch(rng, dtype=W.DTYPE_BF16, Hq=Hq, Hkv=Hkv, d=d, prefix=[P], trees=[tree],
-                     tokens=[W.distinct_sibling_tokens(rng, tree, 500)], Voc=500, p_match=0.7, Nmax=N,
-                     label=f"{splits} splits, {4 * N} rows")
-    U.log(f"[merge] splits={splits} d={d} N={N} P={P}")
-    got = U.gpu_attention(b, U.upload(b))
-    U.compare_attention(b, got, U.oracle_attention(b))
+    _check(Hq, Hkv, N, d, P, f"{splits} splits, {4 * N} rows")
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("P", [700, 3000])
+@pytest.mark.parametrize("N", [1, 3, 4, 5, 15, 16, 17, 64, 65, 129, 255])
+def test_rows(N, P, d):
+    """Rows next to a multiple of 4 and of 16, a merge workgroup's: both merges
+    (4 to 7 and more than 8 splits) stop after the call's rows."""
+    _check(2, 2, N, d, P, f"{N} rows")
