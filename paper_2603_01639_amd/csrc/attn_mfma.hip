@@ -324,9 +324,9 @@ __device__ __forceinline__ void attend(const MfmaArgs& a, Smem& sm, int b, int g
   // ---- Q rows and parent links, straight into LDS ahead of everything else
   // (the tile loads queue behind them, and the wait for them below leaves the
   // first tiles in flight).  A wave's 32 stacked rows row0 + 32 rb + R (its own,
-  // or with two key groups its pair's) land at 256*R in its 8 KiB block, with 16-byte chunk c at c ^ (R & 15), the
-  // layout the K operand also uses; rows past valid_rows repeat the last
-  // valid row (their results are never stored).
+  // or with two key groups its pair's) land at 256*R in its 8 KiB block, with
+  // 16-byte chunk c at c ^ (R & 15), the layout the K operand also uses; rows
+  // past valid_rows repeat the last valid row (their results are never stored).
   const int qrow_idx = row0 + rb * 32 + l32;
   const bool qvalid = qrow_idx < valid_rows;
   // A wave whose 32 rows are all padding only loads tiles and takes part in
@@ -1089,9 +1089,9 @@ __device__ __forceinline__ int merge_splits(const MfmaArgs& a, int b, int row) {
 // launch is latency-bound, so the (m, l) pairs and the first 32 splits' rows are
 // then requested before the sequence's prefix length and node count arrive
 // (kEarly): every row of the grid is inside the workspace's Mpad rows, and
-// every split index below max_splits inside its splits.  (A second round for the splits past 16
-// and reductions through the LDS crossbar made it 5.0 us instead of 4.1 for
-// 240 rows of 17 splits on 8 kv heads.)
+// every split index below max_splits inside its splits.  (A second round for the
+// splits past 16 and reductions through the LDS crossbar made it 5.0 us instead
+// of 4.1 for 240 rows of 17 splits on 8 kv heads.)
 template <int HD, bool kEarly>
 __global__ void __launch_bounds__(256) attn_split_merge_kernel(MfmaArgs a) {
   __shared__ float w_s[4][kMaxMergeSplits];
