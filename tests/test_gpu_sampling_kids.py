@@ -20,3 +20,16 @@ def test_children_across_words(n):
             trees[-1][0] = -1
     S._check(W.make_sampling_batch(rng, trees, 3001, temperature=1.0, draft_noise=3.0,
                                    label=f"children across words n={n}"))
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6])
+def test_last_nodes(n):
+    """The first nodes that no longer have one, two or three nodes after them,
+    hence no such child: stars, chains and stars below a chain."""
+    rng = W.rng_for(750 + n)
+    trees = [W.tree_star(n), W.tree_chain(n)]
+    for top in (1, 2, 3):
+        if top < n:
+            trees.append([j - 1 if j <= top else top for j in range(n)])
+    S._check(W.make_sampling_batch(rng, trees, 3001, temperature=1.0, draft_noise=3.0,
+                                   label=f"last nodes n={n}"))
