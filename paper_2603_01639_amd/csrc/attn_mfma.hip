@@ -1588,7 +1588,7 @@ void plan_split(const AttnShape& s, int num_cus, AttnPlan* p) {
   // the others.  (Half-size units for longer trees too, to leave fewer compute
   // units idle, were slower: 240 rows over a prefix of 2048 on 8 kv heads
   // 14.1 us in 144 workgroups instead of 13.5 in 136.)
-  p->tile_rows = two_key_groups(s) ? kTileRows / 2 : kTileRows;
+  p->tile_rows = rows <= kTileRows / 2 ? kTileRows / 2 : kTileRows;  // (halves a short call's workspace)
   p->row_tiles = (rows + p->tile_rows - 1) / p->tile_rows;
   const double tile = two_key_groups(s) ? kHalfTile : 1.0;
   const int64_t units = static_cast<int64_t>(s.B) * s.Hkv * p->row_tiles;

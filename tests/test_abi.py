@@ -40,6 +40,15 @@ def test_version_and_workspace_queries():
     assert ltd.attn_grid(1, 300, 32, 8, 128, 2048, ltd.DTYPE_BF16, 4096) == -1  # Nmax > 256
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("prefix", [256, 2048, 16384])
+def test_short_calls_take_half_the_workspace(prefix, d):
+    """One sequence of up to 128 stacked rows (16, 17 and 32 nodes of 4 heads)
+    has units of 128 rows, a longer one (33) of 256, however many key groups."""
+    size = [ltd.attn_workspace_size(1, n, 32, 8, d, prefix, ltd.DTYPE_BF16) for n in (1, 16, 17, 32, 33)]
+    assert size == [size[0]] * 4 + [2 * size[0]], size
+
+
 def test_library_links_only_hip_runtime():
     """The product library must not reach the oracle."""
     data = open(ltd.LIB_PATH, "rb").read()

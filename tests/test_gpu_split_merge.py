@@ -1,7 +1,7 @@
 """The split plan's merge kernels on both sides of the rule that picks between
 them (at most 8 splits: 16 lanes a row; more: a wave a row), of the splits
 the wave kernel requests up front (32) and of the splits it weights per lane
-(64), for units of 128 rows (two key groups) and of 256 rows (one)."""
+(64), for units of 128 rows (with two key groups and with one) and of 256."""
 import numpy as np
 import pytest
 import torch  # noqa: F401  (its HIP runtime is loaded before the library asks for the device)
@@ -36,7 +36,7 @@ def _check(Hq, Hkv, N, d, P, label):
 
 
 @pytest.mark.parametrize("d", [128, 64])
-@pytest.mark.parametrize("N,splits", [(33, 3)] + [(N, s) for N in (16, 33) for s in (8, 9, 32, 33, 63, 64, 65)])
+@pytest.mark.parametrize("N,splits", [(33, 3)] + [(N, s) for N in (16, 32, 33) for s in (8, 9, 32, 33, 63, 64, 65)])
 def test_split_counts(N, splits, d):
     Hq, Hkv = 8, 2  # 4 rows a node
     P = _prefix_with_splits(splits, N, Hq, Hkv, d)
